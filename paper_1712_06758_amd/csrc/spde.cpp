@@ -55,7 +55,7 @@ spde_status fail(spde_status s, const char* fmt, ...) {
 
 const char* kKernelNames[KID_COUNT] = {
     "init", "mg_down_fine", "mg_down", "mg_coarse", "mg_up", "mg_up_fine",
-    "scalar", "operator", "output", "flux", "resid", "spmm", "restrict_noise", "spmm_stage"};
+    "scalar", "operator", "output", "flux", "resid", "spmm", "restrict_noise", "spmm_stage", "direction"};
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -66,7 +66,7 @@ namespace spde {
 struct LaunchRec {
   int kid;
   int iter;          // MINRES iteration of the launch (0 outside the loop)
-  int level;         // multigrid level of a level kernel
+  int level;         // multigrid level of a level kernel; iterations of a direction pass
   int s0, nslots;    // slots of the launch (nslots < 0: the whole batch)
   hipEvent_t e0, e1;
   double bytes;      // algorithmic bytes of the whole launch, or < 0: per slot from slot_bytes
@@ -109,6 +109,9 @@ struct Ctx {
   bool mg_cellwise = false;     // the kappa field enters the multigrid (Galerkin coarse kappa^2)
   bool mg_dirty = false;        // the level diagonals must be rebuilt before the next solve
   double* resid_out = nullptr;  // [max_batch]
+  int ring = kRing;             // entries of the zhat ring (kRing or 2)
+  int unapplied = 0;            // iterations enqueued since the last direction pass (at most ring)
+  int slots_hi = 0;             // slots [0, slots_hi) have been initialised since the workspace was bound
   hipStream_t own_stream = nullptr;
   hipStream_t aux_stream = nullptr;   // second half of a split batch
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -131,7 +134,7 @@ struct Ctx {
   int poll = 8;
   std::map<int64_t, hipGraphExec_t> graphs;   // (first slot, half-iterations, batch) -> graph
   int split = 1;                 // 2: batches of 8+ run as two halves on two streams
-  int expect_iters = 0;          // iterations (incl. the finishing pass) the last call needed
+  int expect_iters = 0;          // iterations (incl. the one that finds convergence) the last call needed
   double refine_target = 0.0;     // > 0: refine until ||F - A U|| / ||F|| <= target (float64 residuals)
   int refine_max = 0;             // at most this many refinement passes
   bool tuned = false;
@@ -228,7 +231,10 @@ size_t layout(Ctx* c, char* base) {
   };
   for (int p = 0; p < 2; ++p) c->F.vs[p] = (double*)take(B * 3 * nc * 8);
   for (int p = 0; p < 2; ++p) c->F.vu[p] = (double*)take(B * nc * 8);
-  for (int p = 0; p < 2; ++p) c->F.z[p] = (void*)take(B * nc * c->szm());
+  c->ring = (double)B * (double)nc * (double)c->szm() * kRing <= kRingBytes ? kRing : 2;
+  c->F.z = (void*)take((size_t)c->ring * B * nc * c->szm());
+  c->F.zstr = (int64_t)B * nc;
+  c->F.zm = c->ring - 1;
   for (int p = 0; p < 2; ++p) c->F.w[p] = (double*)take(B * nc * 8);
   c->F.x = (double*)take(B * nc * 8);
   for (int l = 1; l <= c->top && l < c->nlev; ++l) {
@@ -245,6 +251,7 @@ size_t layout(Ctx* c, char* base) {
   c->F.part_up = (double*)take(B * (size_t)c->nb_up0 * 2 * 8);
   c->F.part_pb = (double*)take(B * (size_t)c->nb_pb * 2 * 8);
   c->F.sc = (Scalars*)take(B * sizeof(Scalars));
+  c->F.dir = (DirCoef*)take(B * (size_t)c->ring * sizeof(DirCoef));
   c->resid_out = (double*)take(B * 8);
   return off;
 }
@@ -287,25 +294,17 @@ struct Timed {
 
 // Algorithmic bytes of one launch for one slot (compulsory HBM traffic of the
 // method's data: every input read once, every output written once).
-double slot_bytes(const Ctx* c, int kid, int level, int iter, int wmode_active) {
+double slot_bytes(const Ctx* c, int kid, int level, int iter) {
   const double nc = (double)c->box.nc, sz = (double)c->szm();
   switch (kid) {
     case KID_OPERATOR: {
-      // v update (iterations 1..J): read v_j (faces 24, cell 8), v_{j-1} (32, from j = 2), zhat_j;
-      // write v_{j+1} (32).  Direction update (iterations 1..J): read W_j (j >= 2) and W_{j-1}
-      // (j >= 3), write W_{j+1}.  x: written alone at j = 2, read and written on later even passes
-      // and on the finishing pass J + 1, which reads W_J and W_{J-1} and writes nothing else.
-      double b = 0;
-      const bool fin = (wmode_active & 4) != 0;
-      if (wmode_active & 1) b += nc * ((iter > 1 ? 64.0 : 32.0) + sz + 32.0 + (c->box.kap ? 8.0 : 0.0));
-      if ((wmode_active & 2) && !fin) b += nc * (8.0 + (iter >= 2 ? 8.0 : 0.0) + (iter >= 3 ? 8.0 : 0.0));
-      if (fin) b += nc * (8.0 + (iter >= 4 ? 8.0 : 0.0));
-      if ((wmode_active & 2) && iter >= 2) {
-        if (iter == 2) b += nc * 8.0;
-        else if ((iter % 2) == 0 || fin) b += nc * 16.0;
-      }
-      return b;
+      // iterations 1..J: read v_j (faces 24, cell 8), v_{j-1} (32, from j = 2), zhat_j; write v_{j+1} (32)
+      return nc * ((iter > 1 ? 64.0 : 32.0) + sz + 32.0 + (c->box.kap ? 8.0 : 0.0));
     }
+    case KID_DIRECTION:
+      // `level` iterations up to `iter`: read their zhat, W twice and x (none of them before the first
+      // pass of a solve); write W twice and x
+      return nc * ((double)level * sz + (iter > level ? 24.0 : 0.0) + 24.0);
     case KID_MG_UP_FINE: return nc * (8.0 + sz / 8.0 + 24.0 + sz + (c->box.kap ? 8.0 : 0.0));
     case KID_MG_DOWN_FINE: return nc * (8.0 + sz / 8.0);
     case KID_MG_DOWN: { const double m = (double)c->lv[level].nc; return m * (sz + sz / 8.0); }
@@ -346,9 +345,10 @@ View make_view(const Ctx* c, int s0) {
   for (int p = 0; p < 2; ++p) {
     V.F.vs[p] += (int64_t)s0 * 3 * nc;
     V.F.vu[p] += (int64_t)s0 * nc;
-    V.F.z[p] = (char*)c->F.z[p] + (size_t)s0 * nc * sz;
     V.F.w[p] += (int64_t)s0 * nc;
   }
+  V.F.z = (char*)c->F.z + (size_t)s0 * nc * sz;
+  V.F.dir += (int64_t)s0 * c->ring;
   V.F.x += (int64_t)s0 * nc;
   V.F.part_up += (int64_t)s0 * tiles_for(eff_up(c, 0), c->n) * 2;
   V.F.part_pb += (int64_t)s0 * c->nb_pb;
@@ -361,7 +361,7 @@ View make_view(const Ctx* c, int s0) {
 }
 
 spde_status enqueue_vcycle(Ctx* c, const View& V, int batch, hipStream_t st, int iter, const void* b0,
-                           const void* b1, void* o0, void* o1, const Scalars* sc, double* part) {
+                           const void* b1, void* o, int64_t ostr, int om, const Scalars* sc, double* part) {
   const bool f64 = c->fp64();
   const int s0 = V.s0;
   {
@@ -380,12 +380,12 @@ spde_status enqueue_vcycle(Ctx* c, const View& V, int batch, hipStream_t st, int
   }
   for (int l = c->top - 1; l >= 1; --l) {
     Timed t(c, KID_MG_UP, iter, st, l, s0, batch);
-    HIPCHK(launch_mg_up(f64, eff_up(c, l), false, V.mgb[l], V.mgb[l], V.mge[l + 1], V.mge[l], V.mge[l],
+    HIPCHK(launch_mg_up(f64, eff_up(c, l), false, V.mgb[l], V.mgb[l], V.mge[l + 1], V.mge[l], 0, 0,
                         c->lv[l], batch, sc, nullptr, nullptr, nullptr, c->box, st));
   }
   {
     Timed t(c, KID_MG_UP_FINE, iter, st, 0, s0, batch);
-    HIPCHK(launch_mg_up(f64, eff_up(c, 0), true, b0, b1, V.mge[1], o0, o1, c->lv[0], batch, sc,
+    HIPCHK(launch_mg_up(f64, eff_up(c, 0), true, b0, b1, V.mge[1], o, ostr, om, c->lv[0], batch, sc,
                         V.F.vs[0], V.F.vs[1], part, c->box, st));
   }
   return SPDE_OK;
@@ -393,8 +393,8 @@ spde_status enqueue_vcycle(Ctx* c, const View& V, int batch, hipStream_t st, int
 
 // One MINRES iteration without its operator pass: V-cycle and scalars.
 spde_status enqueue_vpart(Ctx* c, const View& V, int batch, hipStream_t st, int iter) {
-  spde_status s = enqueue_vcycle(c, V, batch, st, iter, V.F.vu[0], V.F.vu[1], V.F.z[0], V.F.z[1], V.F.sc,
-                                 V.F.part_up);
+  spde_status s = enqueue_vcycle(c, V, batch, st, iter, V.F.vu[0], V.F.vu[1], V.F.z, V.F.zstr, V.F.zm,
+                                 V.F.sc, V.F.part_up);
   if (s != SPDE_OK) return s;
   Timed t(c, KID_SCALAR, iter, st, 0, V.s0, batch);
   HIPCHK(launch_scalar(V.F, tiles_for(eff_up(c, 0), c->n), c->nb_pb, batch, st));
@@ -405,6 +405,21 @@ spde_status enqueue_operator(Ctx* c, const View& V, int batch, hipStream_t st, i
   Timed t(c, KID_OPERATOR, iter, st, 0, V.s0, batch);
   HIPCHK(launch_operator(c->fp64(), V.F, c->box, batch, st));
   return SPDE_OK;
+}
+
+// Direction pass over the slots of V (`count` iterations up to `iter` are waiting).
+spde_status enqueue_direction(Ctx* c, const View& V, int batch, hipStream_t st, int iter, int count) {
+  Timed t(c, KID_DIRECTION, iter, st, count, V.s0, batch);
+  HIPCHK(launch_direction(c->fp64(), V.F, c->box, batch, st));
+  return SPDE_OK;
+}
+
+// Apply every slot's waiting direction and solution updates.
+spde_status apply_waiting(Ctx* c, hipStream_t st, int iter) {
+  if (!c->unapplied || !c->slots_hi) return SPDE_OK;
+  spde_status s = enqueue_direction(c, make_view(c, 0), c->slots_hi, st, iter, c->unapplied);
+  if (s == SPDE_OK) c->unapplied = 0;
+  return s;
 }
 
 spde_status enqueue_iteration(Ctx* c, const View& V, int batch, hipStream_t st, int iter) {
@@ -455,11 +470,13 @@ bool launch_graph(Ctx* c, const View& V, int batch, hipStream_t st, int L) {
 // (both parities of the iteration number occur).
 constexpr int kTimedStride = 3;
 
-// `count` iterations for the slots of V: a captured graph if graphs are on
-// and count is the poll interval, else plain launches.  In timing mode 2 the
-// operator passes k = 0, 3, 6, ... of the block are launched on their own,
-// bracketed by an event pair, and everything between them replays as graphs.
-spde_status enqueue_block(Ctx* c, const View& V, int batch, hipStream_t st, bool graphs, int iter0, int count) {
+// `count` iterations (at most the ring's entries) for the slots of V: a captured
+// graph if `whole` (a full block of the poll interval) and graphs are on, else
+// plain launches.  In timing mode 2 the operator passes k = 0, 3, 6, ... of the
+// block are launched on their own, bracketed by an event pair, and everything
+// between them replays as graphs.
+spde_status enqueue_chunk(Ctx* c, const View& V, int batch, hipStream_t st, bool graphs, bool whole, int iter0,
+                          int count) {
   if (graphs && c->timing == 2) {
     bool ok = launch_graph(c, V, batch, st, 1);   // V-part of iteration 0
     for (int k = 0; ok && k < count; k += kTimedStride) {
@@ -473,12 +490,32 @@ spde_status enqueue_block(Ctx* c, const View& V, int batch, hipStream_t st, bool
     if (ok) return SPDE_OK;
     return fail(SPDE_EHIP, "graph launch failed in timing mode 2");
   }
-  if (graphs && c->timing == 0 && count == c->poll) {
-    if (launch_graph(c, V, batch, st, 2 * c->poll)) return SPDE_OK;
+  if (graphs && c->timing == 0 && whole) {
+    if (launch_graph(c, V, batch, st, 2 * count)) return SPDE_OK;
   }
   for (int k = 0; k < count; ++k) {
     spde_status s = enqueue_iteration(c, V, batch, st, iter0 + k + 1);
     if (s != SPDE_OK) return s;
+  }
+  return SPDE_OK;
+}
+
+// `count` iterations for the slots of V, *unapplied of whose predecessors still
+// wait for a direction pass; a pass runs whenever the ring would overflow.
+spde_status enqueue_block(Ctx* c, const View& V, int batch, hipStream_t st, bool graphs, int iter0, int count,
+                          int* unapplied) {
+  const bool whole = count == c->poll;
+  for (int done = 0; done < count;) {
+    const int chunk = std::min(count - done, c->ring);
+    if (*unapplied + chunk > c->ring) {
+      spde_status s = enqueue_direction(c, V, batch, st, iter0 + done, *unapplied);
+      if (s != SPDE_OK) return s;
+      *unapplied = 0;
+    }
+    spde_status s = enqueue_chunk(c, V, batch, st, graphs, whole, iter0 + done, chunk);
+    if (s != SPDE_OK) return s;
+    *unapplied += chunk;
+    done += chunk;
   }
   return SPDE_OK;
 }
@@ -512,16 +549,14 @@ void close_timing(Ctx* c, int batch) {
     double bytes = r.bytes >= 0.0 ? r.bytes : 0.0;
     const int s_end = r.bytes >= 0.0 ? r.s0 : (r.nslots < 0 ? batch : std::min(batch, r.s0 + r.nslots));
     for (int s = r.s0; s < s_end; ++s) {
-      const bool done = states[s] == ST_DONE || states[s] == ST_FINISH;
-      const int J = done ? iters[s] : (1 << 30);
+      const int J = states[s] == ST_DONE ? iters[s] : (1 << 30);
       if (r.kid == KID_OPERATOR) {
-        int mode = 0;
-        if (r.iter <= J) mode |= 1;
-        if (r.iter >= 1 && r.iter <= J + 1) mode |= 2;
-        if (r.iter == J + 1) mode |= 4;
-        bytes += slot_bytes(c, r.kid, 0, r.iter, mode);
+        if (r.iter <= J) bytes += slot_bytes(c, r.kid, 0, r.iter);
+      } else if (r.kid == KID_DIRECTION) {
+        const int last = std::min(r.iter, J + 1), m = last - (r.iter - r.level);
+        if (m > 0) bytes += slot_bytes(c, r.kid, m, last);
       } else if (r.iter >= 1 && r.iter <= J + 1) {
-        bytes += slot_bytes(c, r.kid, r.level, r.iter, 0);
+        bytes += slot_bytes(c, r.kid, r.level, r.iter);
       }
     }
     c->t_ms[r.kid] += ms;
@@ -634,7 +669,7 @@ spde_status autotune(Ctx* c, hipStream_t st) {
     for (int l = 0; l < c->top; ++l) {
       const bool fine = l == 0;
       const void* bsrc = fine ? (const void*)c->F.vu[0] : c->mgb[l];
-      void* osrc = fine ? c->F.z[0] : c->mge[l];
+      void* osrc = fine ? c->F.z : c->mge[l];
       float best = 1e30f;
       for (int sh = 0; sh < kNumShapes; ++sh) {
         if (!shape_ok_down(sh, f64)) continue;
@@ -654,7 +689,7 @@ spde_status autotune(Ctx* c, hipStream_t st) {
         // output; how much of it is still in the caches depends on the tile
         // order, so the two are timed together.
         spde_status s = time_launches(c, st, [&] {
-          hipError_t e = launch_mg_up(f64, sh, fine, bsrc, bsrc, c->mge[l + 1], osrc, osrc, c->lv[l], B, nullptr,
+          hipError_t e = launch_mg_up(f64, sh, fine, bsrc, bsrc, c->mge[l + 1], osrc, 0, 0, c->lv[l], B, nullptr,
                                       c->F.vs[0], c->F.vs[0], fine ? c->F.part_up : nullptr, c->box, st);
           if (e == hipSuccess && fine) e = launch_operator(f64, c->F, c->box, B, st);
           return e;
@@ -889,6 +924,8 @@ spde_status spde_bind_workspace(spde_handle h, void* dev_ptr, size_t bytes) {
   const size_t need = workspace_size(c);
   if (bytes < need) return fail(SPDE_ENOMEM, "workspace has %zu bytes, %zu needed", bytes, need);
   layout(c, (char*)dev_ptr);
+  c->unapplied = 0;
+  c->slots_hi = 0;
   c->ws = (char*)dev_ptr;
   c->ws_bytes = bytes;
   HIPCHK(prepare_coarse(c->fp64(), c->coarse_lds));
@@ -1071,6 +1108,10 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
   if (s != SPDE_OK) return s;
   s = prepare_mg_coeffs(c, st);
   if (s != SPDE_OK) return s;
+  // updates that other slots of the handle still wait for
+  s = apply_waiting(c, st, 0);
+  if (s != SPDE_OK) return s;
+  c->slots_hi = std::max(c->slots_hi, batch);
   // the load F_u: the caller's noise, or the generated noise drawn again into
   // a Lanczos buffer that no running solve uses
   const double* xi_res = src.xi;
@@ -1147,11 +1188,16 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
     while (!all_done && launched < cap + c->poll) {
       int count = c->poll;
       if (expect > launched) count = std::min(count, expect - launched);
-      spde_status s2 = enqueue_block(c, V0, b1, st, graphs, launched, count);
-      if (s2 != SPDE_OK) return s2;
+      int waiting = c->unapplied;   // the same for both halves
       if (split) {
-        s2 = enqueue_block(c, V1, batch - b1, c->aux_stream, graphs, launched, count);
+        int w1 = waiting;
+        spde_status s2 = enqueue_block(c, V1, batch - b1, c->aux_stream, graphs, launched, count, &w1);
         if (s2 != SPDE_OK) return s2;
+      }
+      spde_status s2 = enqueue_block(c, V0, b1, st, graphs, launched, count, &waiting);
+      if (s2 != SPDE_OK) return s2;
+      c->unapplied = waiting;
+      if (split) {
         HIPCHK(hipEventRecord(c->ev_join, c->aux_stream));
         HIPCHK(hipStreamWaitEvent(st, c->ev_join, 0));
       }
@@ -1163,7 +1209,7 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
         if (c->host_sc[b].state == ST_ACTIVE) { all_done = false; break; }
       }
     }
-    return SPDE_OK;
+    return apply_waiting(c, st, launched);
   };
   int launched = 0;
   s = iterate(c->expect_iters, launched);
@@ -1177,9 +1223,9 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
     if (sc.state == ST_FAILED) { failed = true; bad[b] = 1; }
     if (sc.state == ST_ACTIVE || (sc.flags & FL_NOTCONV)) notconv = true;
     total[b] = sc.state == ST_ACTIVE ? launched : sc.iters;
-    if (sc.state == ST_FINISH || sc.state == ST_DONE) most = std::max(most, sc.iters);
+    if (sc.state == ST_DONE) most = std::max(most, sc.iters);
   }
-  // a converged sample needs its iterations plus the finishing pass
+  // a converged sample needs its iterations and the V-part that finds it converged
   c->expect_iters = (!notconv && !failed && most > 0) ? most + 1 : 0;
   HIPCHK(launch_fix_solution(c->F, bx, batch, 0, st));
   // Iterative refinement in float64: with r = F - A U (flux recovered from U,
@@ -1353,6 +1399,7 @@ spde_status spde_slots_reset(spde_handle h, int nslots, void* stream) {
   s = prepare_mg_coeffs(c, st);
   if (s != SPDE_OK) return s;
   HIPCHK(launch_set_state(c->F.sc, 0, nslots, ST_IDLE, st));
+  c->slots_hi = std::max(c->slots_hi, nslots);
   return SPDE_OK;
 }
 
@@ -1366,6 +1413,7 @@ spde_status spde_slot_start(spde_handle h, int slot, const double* xi_dev, void*
   hipStream_t st = pick_stream(c, stream);
   const double scale = -c->g * std::pow(c->box.h, 1.5);
   HIPCHK(launch_init(c->F, c->box, xi_dev, scale, 1, c->rtol, c->max_iter, slot, st));
+  c->slots_hi = std::max(c->slots_hi, slot + 1);
   return SPDE_OK;
 }
 
@@ -1382,6 +1430,7 @@ spde_status spde_slot_start_seeded(spde_handle h, int slot, uint64_t seed, uint6
   hipStream_t st = pick_stream(c, stream);
   const double scale = -c->g * std::pow(c->box.h, 1.5);
   HIPCHK(launch_init_gen(c->F, c->box, seed, event, coupled, scale, 1, c->rtol, c->max_iter, slot, st));
+  c->slots_hi = std::max(c->slots_hi, slot + 1);
   return SPDE_OK;
 }
 
@@ -1394,24 +1443,33 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = pick_stream(c, stream);
   const bool graphs = c->use_graphs && c->timing != 1 && st != nullptr;
-  int done = 0;
   const View V0 = make_view(c, 0);
-  while (done < iters) {
-    hipGraphExec_t ex = nullptr;
-    if (graphs && iters - done >= c->poll && get_graph(c, V0, nslots, st, &ex, 2 * c->poll) != SPDE_OK) {
-      hipGetLastError();
-      c->use_graphs = false;
-      ex = nullptr;
-    }
-    if (ex) {
-      HIPCHK(hipGraphLaunch(ex, st));
-      done += c->poll;
-    } else {
-      s = enqueue_iteration(c, V0, nslots, st, 0);
-      if (s != SPDE_OK) return s;
-      done += 1;
-    }
+  // A caller may be capturing the stream and replay these launches any number
+  // of times: the direction passes are then part of what is captured, with
+  // nothing left waiting before or after.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) { hipGetLastError(); cap = hipStreamCaptureStatusNone; }
+  const bool captured = cap == hipStreamCaptureStatusActive;
+  c->slots_hi = std::max(c->slots_hi, nslots);
+  if (captured) {
+    s = enqueue_direction(c, V0, c->slots_hi, st, 0, c->ring);
+    if (s != SPDE_OK) return s;
   }
+  int waiting = captured ? 0 : c->unapplied;
+  for (int done = 0; done < iters;) {
+    const int chunk = std::min({iters - done, c->poll, c->ring});
+    if (waiting + chunk > c->ring) {
+      s = enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
+      if (s != SPDE_OK) return s;
+      waiting = 0;
+    }
+    s = enqueue_chunk(c, V0, nslots, st, graphs && !captured, chunk == std::min(c->poll, c->ring), 0, chunk);
+    if (s != SPDE_OK) return s;
+    waiting += chunk;
+    if (!captured) c->unapplied = waiting;
+    done += chunk;
+  }
+  if (captured) return enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
   return SPDE_OK;
 }
 
@@ -1429,7 +1487,6 @@ spde_status spde_slots_poll(spde_handle h, int nslots, int* state_host, int* ite
     int code;
     switch (v.state) {
       case ST_ACTIVE: code = 0; break;
-      case ST_FINISH:
       case ST_DONE: code = (v.flags & FL_NOTCONV) ? 2 : 1; break;
       case ST_FAILED: code = 3; break;
       default: code = 4;
@@ -1447,6 +1504,8 @@ spde_status spde_slot_finish(spde_handle h, int slot, double* u_box_dev, void* s
   if (slot < 0 || slot >= c->max_batch) return fail(SPDE_EINVAL, "slot out of range");
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = pick_stream(c, stream);
+  s = apply_waiting(c, st, 0);
+  if (s != SPDE_OK) return s;
   HIPCHK(launch_fix_solution(c->F, c->box, 1, slot, st));
   if (u_box_dev)
     HIPCHK(hipMemcpyAsync(u_box_dev, c->F.x + cell_off(slot, c->box.nc), c->box.nc * 8, hipMemcpyDeviceToDevice,
@@ -1513,7 +1572,8 @@ spde_status spde_apply_operator(spde_handle h, int batch, const double* x_sigma_
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = pick_stream(c, stream);
   Fields G = c->F;
-  G.z[0] = G.w[0];            // a float64 cell buffer for zhat = x_u
+  G.z = G.w[0];               // a float64 cell buffer for zhat = x_u
+  G.zm = 0;
   Box bd = c->box;
   bd.poly = 0;                // face block diag(M)^-1: the pass then computes A x itself
   HIPCHK(launch_ext_to_int(x_sigma_dev, x_u_dev, G, bd, batch, st));
@@ -1549,15 +1609,15 @@ spde_status spde_apply_vcycle(spde_handle h, int batch, const double* r_dev, dou
   if (!r_dev || !z_dev) return fail(SPDE_EINVAL, "null pointer");
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = pick_stream(c, stream);
-  void* out = c->fp64() ? (void*)z_dev : c->F.z[0];
+  void* out = c->fp64() ? (void*)z_dev : c->F.z;
   s = autotune(c, st);
   if (s != SPDE_OK) return s;
   s = prepare_mg_coeffs(c, st);
   if (s != SPDE_OK) return s;
   // the finest up kernel always writes partial sums: give it the solver's buffer
-  s = enqueue_vcycle(c, make_view(c, 0), batch, st, 0, r_dev, r_dev, out, out, nullptr, c->F.part_up);
+  s = enqueue_vcycle(c, make_view(c, 0), batch, st, 0, r_dev, r_dev, out, 0, 0, nullptr, c->F.part_up);
   if (s != SPDE_OK) return s;
-  if (!c->fp64()) HIPCHK(launch_f32_to_f64((const float*)c->F.z[0], z_dev, (int64_t)batch * c->box.nc, st));
+  if (!c->fp64()) HIPCHK(launch_f32_to_f64((const float*)c->F.z, z_dev, (int64_t)batch * c->box.nc, st));
   return SPDE_OK;
 }
 

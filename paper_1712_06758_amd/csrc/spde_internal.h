@@ -21,8 +21,7 @@ constexpr int kBlock = 256;          // threads per block of the streaming kerne
 // Per-sample solver state (one per batch slot).
 enum SlotState : int {
   ST_ACTIVE = 0,   // iterating
-  ST_FINISH = 1,   // converged or capped: the operator pass applies the last x update
-  ST_DONE   = 2,   // solution final in x
+  ST_DONE   = 2,   // converged or capped (its last solution updates may still wait in the ring)
   ST_FAILED = 3,   // breakdown / non-finite
   ST_IDLE   = 4    // slot not in use
 };
@@ -47,24 +46,39 @@ struct alignas(16) Scalars {
   double zs;                  // 1 / gamma_j
   double a_v;                 // delta_j / gamma_j
   double b_v;                 // gamma_j / gamma_{j-1}
-  // Directions are stored unnormalised, W_{j+1} = alpha1_j w_{j+1}, so that the
-  // operator pass of iteration j can form W_{j+1} from zhat_j before alpha1_j
-  // (which needs gamma_{j+1}) is known:
-  //   W_{j+1} = zs zhat_j + ww W_j + ww_prev W_{j-1};  x += xw W_j (+ xpend W_{j-1})
-  double ww, ww_prev;
-  double xw;                  // coefficient of W_j in the solution update
-  double xpend;               // coefficient of W_{j-1} whose x update was deferred (0 if none)
   double al1_prev;            // alpha1 of the previous Givens step
   double tol;                 // relative stopping tolerance on |eta| / eta0
   int it;                     // iteration the V-cycle and the scalar step work on
   int pit;                    // iteration the operator pass works on
   int state;
   int flags;
-  int wmode;                  // -1 no w/x update, 0 first (no reads), 1 no W_{j-1}, 2 full
   int iters;                  // iterations when finished
   int max_iter;
-  int pad;
+  int jf;                     // iterations whose direction and solution updates are in W and x
+  int dblk;                   // blocks of a running direction pass that have ended
 };
+
+// Direction and solution updates of iteration j, waiting in the ring until the
+// direction pass applies them.  Directions are stored unnormalised, W_{j+1} =
+// alpha1_j w_{j+1}, so that all coefficients are known after the scalar step of
+// iteration j:  x += xw W_j;  W_{j+1} = zs zhat_j + ww W_j + ww_prev W_{j-1}.
+struct alignas(16) DirCoef {
+  double zs, ww, ww_prev, xw;
+};
+
+// Iterations the ring of zhat holds between two direction passes (a power of
+// two).  Both updates are local to a cell, so they can wait: the operator pass
+// then leaves W and x alone (32 of its 132 bytes per cell in mixed precision),
+// and one direction pass moves 48 + kRing sizeof(zhat) bytes per cell for kRing
+// iterations.  Operator pass with the updates, without them, and direction pass
+// per iteration: 3.37 -> 2.56 + 0.31 ms (mixed, 128^3 x 64), 188 -> 148 + 16 us
+// (float64, 64^3 x 32).  At 128^3 x 1 in float64, where the old pass ran out of
+// the last-level cache: 45.5 -> 38.7 + 5.1 us; 8 entries would leave 7.8 us
+// there, since each pass brings W and x back from memory.  The ring costs kRing
+// sizeof(zhat) bytes of memory per cell; where that would pass kRingBytes, two
+// entries are kept instead (the memory of a double buffer).
+constexpr int kRing = 16;
+constexpr double kRingBytes = 32.0 * 1024 * 1024 * 1024;
 
 // Box constants.
 struct Box {
@@ -109,6 +123,16 @@ __device__ __forceinline__ void st_stream(T v, T* p) {
 }
 #endif
 
+// The operator and direction passes stream their vectors with the nontemporal
+// hint when those of the launch (about 100 bytes per cell and sample) exceed this
+// size.  MI355X has a 256 MB last-level cache: one 128^3 sample (about 210 MB)
+// runs faster without the hint, since its vectors largely stay cached between
+// passes, two or more run faster with it.
+constexpr double kStreamBytes = 300.0 * 1024 * 1024;
+inline bool streams_past_cache(const Box& b, int batch) {
+  return 100.0 * (double)b.nc * (double)batch > kStreamBytes;
+}
+
 // kappa^2 h^3 of cell c (same rounding as the host's kappa * kappa * h^3).
 // VAR: cell-wise kappa (a compile-time choice in the hot kernels, so that the
 // constant path carries no branch); the run-time form serves the others.
@@ -152,8 +176,12 @@ struct CoarseParams {
 struct Fields {
   double* vs[2];     // face Lanczos vectors: vs[p] + (slot*3 + d) * nc
   double* vu[2];     // cell Lanczos vectors
-  void*   z[2];      // preconditioned cell vectors (float or double)
-  double* w[2];      // MINRES direction vectors (cell part)
+  void*   z;         // preconditioned cell vectors (float or double), a ring of zm + 1
+                     // entries of zstr values: zhat_j is entry j & zm
+  int64_t zstr;
+  int     zm;
+  DirCoef* dir;      // [slot][zm + 1] waiting updates
+  double* w[2];      // MINRES direction vectors (cell part): W_{j+1} in w[j & 1]
   double* x;         // solution (cell part)
   double* part_up;   // [slot][nb_up][2] partial sums of <zhat, v_u>, zhat^T A zhat
   double* part_pb;   // [slot][nb_pb]    partial sums of q |v_sigma|^2
@@ -168,7 +196,7 @@ __host__ __device__ inline int64_t face_off(int slot, int d, int64_t nc) { retur
 enum KernelId : int {
   KID_INIT = 0, KID_MG_DOWN_FINE, KID_MG_DOWN, KID_MG_COARSE, KID_MG_UP, KID_MG_UP_FINE,
   KID_SCALAR, KID_OPERATOR, KID_OUTPUT, KID_FLUX, KID_RESID, KID_SPMM, KID_RESTRICT, KID_SPMM_STAGE,
-  KID_COUNT
+  KID_DIRECTION, KID_COUNT
 };
 
 }  // namespace spde
@@ -202,8 +230,10 @@ hipError_t launch_set_state(Scalars* sc, int slot0, int count, int state, hipStr
 hipError_t launch_tune_scalars(Scalars* sc, int batch, hipStream_t st);
 hipError_t launch_mg_down(bool fp64, int shape, bool fine, const void* b0, const void* b1, void* rH,
                           const Level& L, int batch, const Scalars* sc, hipStream_t st);
-hipError_t launch_mg_up(bool fp64, int shape, bool fine, const void* b0, const void* b1, const void* eH, void* o0,
-                        void* o1, const Level& L, int batch, const Scalars* sc, const double* vs0,
+// The finest level's output of a slot in iteration j goes to o + (j & om) ostr
+// (values); o itself when sc is null and on the coarser levels.
+hipError_t launch_mg_up(bool fp64, int shape, bool fine, const void* b0, const void* b1, const void* eH, void* o,
+                        int64_t ostr, int om, const Level& L, int batch, const Scalars* sc, const double* vs0,
                         const double* vs1, double* part, const Box& bx, hipStream_t st);
 hipError_t prepare_coarse(bool fp64, size_t lds_bytes);
 // the same per level precision (spde_mg_f32.hip / spde_mg_f64.hip)
@@ -211,7 +241,8 @@ hipError_t prepare_coarse(bool fp64, size_t lds_bytes);
   hipError_t launch_mg_down_##NAME(int shape, bool fine, const void* b0, const void* b1, void* rH,            \
                                    const Level& L, int batch, const Scalars* sc, hipStream_t st);             \
   hipError_t launch_mg_up_##NAME(int shape, bool fine, const void* b0, const void* b1, const void* eH,        \
-                                 void* o0, void* o1, const Level& L, int batch, const Scalars* sc,            \
+                                 void* o, int64_t ostr, int om, const Level& L, int batch,                    \
+                                 const Scalars* sc,                                                           \
                                  const double* vs0, const double* vs1, double* part, const Box& bx,           \
                                  hipStream_t st);                                                             \
   hipError_t prepare_coarse_##NAME(size_t lds_bytes);                                                         \
@@ -227,6 +258,9 @@ hipError_t launch_mg_coarse(bool fp64, const void* btop, void* etop, const Coars
 hipError_t launch_coarse_inverse(bool fp64, const Level& L, void* out, hipStream_t st);
 hipError_t launch_scalar(const Fields& F, int nb_up, int nb_pb, int batch, hipStream_t st);
 hipError_t launch_operator(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st);
+// Apply the waiting direction and solution updates of the slots (a slot with
+// none is left as it is).
+hipError_t launch_direction(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st);
 hipError_t launch_fix_solution(const Fields& F, const Box& bx, int batch, int slot0, hipStream_t st);
 hipError_t launch_flux(const double* u, double* sig_int, double* sig_ext, const Box& bx, int batch,
                        hipStream_t st);

@@ -18,7 +18,8 @@
 //   scalar                           : per-slot reductions, Givens rotation,
 //                                      convergence test
 //   operator                         : v_{j+1} = A z_j - (delta/gamma) v_j - (gamma/gamma_prev) v_{j-1}
-//                                      and the delayed w/x update of step j-1
+// and every few iterations
+//   direction                        : the direction and solution updates of those iterations
 #include <mutex>
 
 #include "spde_common.inc"
@@ -30,7 +31,7 @@ namespace spde {
 
 __device__ __forceinline__ void init_scalars(const Fields& F, int slot, double tol, int max_iter) {
   Scalars s{};
-  s.it = 1; s.pit = 0; s.state = ST_ACTIVE; s.flags = 0; s.wmode = -1;
+  s.it = 1; s.pit = 0; s.state = ST_ACTIVE; s.flags = 0; s.jf = 0; s.dblk = 0;
   s.c = s.c_prev = 1.0; s.s = s.s_prev = 0.0;
   s.gamma_prev = 1.0; s.tol = tol; s.max_iter = max_iter; s.iters = 0;
   F.sc[slot] = s;
@@ -80,10 +81,6 @@ __global__ __launch_bounds__(kBlock) void k_scalar(Fields F, int nb_up, int nb_p
   const int slot = blockIdx.x;
   Scalars* S = F.sc + slot;
   const int state = S->state;
-  if (state == ST_FINISH) {
-    if (threadIdx.x == 0) S->state = ST_DONE;
-    return;
-  }
   if (state != ST_ACTIVE) return;
   const int j = S->it;
   double a0 = 0.0, a1 = 0.0;
@@ -104,13 +101,11 @@ __global__ __launch_bounds__(kBlock) void k_scalar(Fields F, int nb_up, int nb_p
   }
   const double gam = sqrt(gg);
   const double del = gg > 0.0 ? a1 / gg : 0.0;
+  DirCoef dc{};
   if (j == 1) {
     s.eta = gam; s.eta0 = gam;
     s.c = s.c_prev = 1.0; s.s = s.s_prev = 0.0;
-    s.wmode = 0;                       // W_2 = z_1
-    s.ww = s.ww_prev = 0.0;
-    s.xw = s.xpend = 0.0;
-    s.al1_prev = 1.0;
+    s.al1_prev = 1.0;                  // W_2 = z_1
     s.b_v = 0.0;
   } else {
     // complete the Givens rotation of step j-1 now that gamma_j is known
@@ -119,27 +114,23 @@ __global__ __launch_bounds__(kBlock) void k_scalar(Fields F, int nb_up, int nb_p
     const double al1 = sqrt(al0 * al0 + gg);
     if (!(al1 > 0.0) || !isfinite(al1)) { s.state = ST_FAILED; s.iters = j - 1; *S = s; return; }
     const double cn = al0 / al1, sn = gam / al1;
-    // x_{j-1} = x_{j-2} + c_j eta w_j with w_j = W_j / alpha1_{j-1}.  The
-    // operator pass of an odd iteration >= 3 defers its solution update to the
-    // next pass (x absorbs two directions every other iteration).
-    s.xpend = ((j - 1) % 2 == 1 && j - 1 >= 3) ? s.xw : 0.0;
-    s.xw = cn * s.eta / al1;
+    // x_{j-1} = x_{j-2} + c_j eta w_j with w_j = W_j / alpha1_{j-1}
+    dc.xw = cn * s.eta / al1;
     s.eta = -sn * s.eta;
     // W_{j+1} = z_j - alpha3_j w_{j-1} - alpha2_j w_j, with
     // alpha2_j = s_j delta_j + c_{j-1} c_j gamma_j and alpha3_j = s_{j-1} gamma_j
     const double a2 = sn * del + s.c * cn * gam;
     const double a3 = s.s * gam;
-    s.ww = -a2 / al1;
-    s.ww_prev = -a3 / s.al1_prev;
+    dc.ww = -a2 / al1;
+    dc.ww_prev = j > 2 ? -a3 / s.al1_prev : 0.0;
     s.al1_prev = al1;
     s.c_prev = s.c; s.s_prev = s.s;
     s.c = cn; s.s = sn;
-    s.wmode = (j == 2) ? 1 : 2;
     s.b_v = gam / gp;
     if (fabs(s.eta) <= s.tol * s.eta0 || gg == 0.0) {
-      s.state = ST_FINISH; s.iters = j - 1;
+      s.state = ST_DONE; s.iters = j - 1;
     } else if (j - 1 >= s.max_iter) {
-      s.state = ST_FINISH; s.iters = j - 1; s.flags |= FL_NOTCONV;
+      s.state = ST_DONE; s.iters = j - 1; s.flags |= FL_NOTCONV;
     }
   }
   s.gamma_prev = (j == 1) ? 1.0 : s.gamma;
@@ -150,6 +141,94 @@ __global__ __launch_bounds__(kBlock) void k_scalar(Fields F, int nb_up, int nb_p
   s.pit = j;
   s.it = j + 1;
   *S = s;
+  dc.zs = s.zs;
+  F.dir[(int64_t)slot * (F.zm + 1) + (j & F.zm)] = dc;
+}
+
+// ---------------------------------------------------------------------------
+// direction pass: the direction and solution updates of the iterations
+// jf + 1 .. pit of each slot, oldest first,
+//   x += xw_j W_j,   W_{j+1} = zs_j zhat_j + ww_j W_j + ww_prev_j W_{j-1},
+// with W and x read and written once for all of them.  Purely local to a cell,
+// so the pass is bound by its bytes: 48 + m sizeof(zhat) per cell for m
+// iterations; V cells per thread make every access 16 bytes wide, and all loads
+// are issued before the first is used.  The products are fused by hand, so that
+// the values do not depend on how many iterations a pass takes.
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef float flt4 __attribute__((ext_vector_type(4)));
+template <typename TZ> struct ZVec;
+template <> struct ZVec<double> { using type = dbl2; };
+template <> struct ZVec<float> { using type = flt4; };
+
+template <typename TZ, bool NT>
+__global__ __launch_bounds__(kBlock) void k_direction(Fields F, int64_t nc, int nb) {
+  using VZ = typename ZVec<TZ>::type;
+  constexpr int V = 16 / sizeof(TZ), H = V / 2;   // cells per thread, double pairs per thread
+  const int lb = xcd_remap(blockIdx.x, gridDim.x);
+  const int slot = lb / nb, blk = lb - slot * nb;
+  Scalars* S = F.sc + slot;
+  const int state = S->state;
+  if (state != ST_ACTIVE && state != ST_DONE) return;
+  const int jf = S->jf, m = min(S->pit - jf, F.zm + 1);
+  if (m <= 0) return;
+  const int64_t c = ((int64_t)blk * kBlock + threadIdx.x) * V;
+  const bool in = c < nc;
+  const int64_t co = cell_off(slot, nc) + (in ? c : 0);
+  // W_{jf+1} in w[jf & 1], W_{jf} in the other; neither exists before the
+  // first update, W_1 never does
+  dbl2* pa = reinterpret_cast<dbl2*>(F.w[jf & 1] + co);
+  dbl2* pb = reinterpret_cast<dbl2*>(F.w[(jf & 1) ^ 1] + co);
+  dbl2* px = reinterpret_cast<dbl2*>(F.x + co);
+  const bool has_a = jf >= 1, has_b = jf >= 2, has_x = jf >= 1 || (S->flags & FL_ACCUM);
+  const TZ* z = reinterpret_cast<const TZ*>(F.z) + co;
+  VZ zz[kRing];
+#pragma unroll
+  for (int k = 0; k < kRing; ++k)
+    if (k < m) zz[k] = ld_stream<NT>(reinterpret_cast<const VZ*>(z + ((jf + 1 + k) & F.zm) * F.zstr));
+  dbl2 a[H], b[H], x[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    a[h] = has_a ? ld_stream<NT>(pa + h) : dbl2{0.0, 0.0};
+    b[h] = has_b ? ld_stream<NT>(pb + h) : dbl2{0.0, 0.0};
+    x[h] = has_x ? ld_stream<NT>(px + h) : dbl2{0.0, 0.0};
+  }
+  // The block that counts itself last moves jf on: by then every block has read
+  // it (no data passes between the blocks, so the count needs no fence).
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int before = __hip_atomic_fetch_add(&S->dblk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before == nb - 1) {
+      S->dblk = 0;
+      S->jf = jf + m;
+    }
+  }
+  if (!in) return;
+  const DirCoef* dir = F.dir + (int64_t)slot * (F.zm + 1);
+#pragma unroll
+  for (int k = 0; k < kRing; ++k) {
+    if (k < m) {
+      const DirCoef dc = dir[(jf + 1 + k) & F.zm];
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          x[h][e] = fma(dc.xw, a[h][e], x[h][e]);
+          const double t = fma(dc.ww_prev, b[h][e], fma(dc.ww, a[h][e], dc.zs * (double)zz[k][2 * h + e]));
+          b[h][e] = a[h][e];
+          a[h][e] = t;
+        }
+      }
+    }
+  }
+  // after m updates W_{jf+m+1} belongs in w[(jf + m) & 1]
+  dbl2* qa = (m & 1) ? pb : pa;
+  dbl2* qb = (m & 1) ? pa : pb;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    qa[h] = a[h];
+    qb[h] = b[h];
+    px[h] = x[h];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -170,8 +249,8 @@ __global__ __launch_bounds__(kBlock) void k_fix_solution(Fields F, Box bx, int n
   const bool fail = S->state == ST_FAILED;
   const bool zero = (S->flags & FL_ZERO) && !(S->flags & FL_ACCUM);
   if (!zero && !fail) return;
-  const int64_t c = (int64_t)blk * kBlock + threadIdx.x;
-  if (c < bx.nc) F.x[cell_off(slot, bx.nc) + c] = zero ? 0.0 : __builtin_nan("");
+  for (int64_t c = (int64_t)blk * kBlock + threadIdx.x; c < bx.nc; c += (int64_t)nb * kBlock)
+    F.x[cell_off(slot, bx.nc) + c] = zero ? 0.0 : __builtin_nan("");
 }
 
 // Flux recovery sigma = -M^-1 B^T u (first block row of eq. linsys): along
@@ -721,7 +800,7 @@ __global__ __launch_bounds__(kBlock) void k_ext_to_int_zhat(const double* __rest
   F.vs[0][face_off(slot, 0, nc) + c] = i > 0 ? e[i + (int64_t)(n + 1) * (j + (int64_t)n * k)] * iq : 0.0;
   F.vs[0][face_off(slot, 1, nc) + c] = j > 0 ? e[nf + i + (int64_t)n * (j + (int64_t)(n + 1) * k)] * iq : 0.0;
   F.vs[0][face_off(slot, 2, nc) + c] = k > 0 ? e[2 * nf + i + (int64_t)n * (j + (int64_t)n * k)] * iq : 0.0;
-  reinterpret_cast<TZ*>(F.z[0])[cell_off(slot, nc) + c] = (TZ)xu[cell_off(slot, nc) + c];
+  reinterpret_cast<TZ*>(F.z)[cell_off(slot, nc) + c] = (TZ)xu[cell_off(slot, nc) + c];
   F.vu[0][cell_off(slot, nc) + c] = 0.0;
 }
 
@@ -739,7 +818,7 @@ __global__ __launch_bounds__(kBlock) void k_ext_to_int(const double* __restrict_
   F.vs[0][face_off(slot, 0, nc) + c] = i > 0 ? e[i + (int64_t)(n + 1) * (j + (int64_t)n * k)] * iq : 0.0;
   F.vs[0][face_off(slot, 1, nc) + c] = j > 0 ? e[nf + i + (int64_t)n * (j + (int64_t)(n + 1) * k)] * iq : 0.0;
   F.vs[0][face_off(slot, 2, nc) + c] = k > 0 ? e[2 * nf + i + (int64_t)n * (j + (int64_t)n * k)] * iq : 0.0;
-  reinterpret_cast<double*>(F.z[0])[cell_off(slot, nc) + c] = xu[cell_off(slot, nc) + c];
+  reinterpret_cast<double*>(F.z)[cell_off(slot, nc) + c] = xu[cell_off(slot, nc) + c];
   F.vu[0][cell_off(slot, nc) + c] = 0.0;
 }
 
@@ -767,18 +846,18 @@ __global__ void k_probe_scalars(Scalars* sc, int batch) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= batch) return;
   Scalars v{};
-  v.state = ST_ACTIVE; v.pit = 0; v.it = 0; v.zs = 1.0; v.a_v = 0.0; v.b_v = 0.0; v.wmode = -1; v.xpend = 0.0;
+  v.state = ST_ACTIVE; v.pit = 0; v.it = 0; v.zs = 1.0; v.a_v = 0.0; v.b_v = 0.0;
   sc[s] = v;
 }
 
-// Scalars of a steady-state iteration (an even pass with the previous vectors
-// and the solution update) for timing the operator pass; the coefficients are
-// zero, so whatever the vectors hold, nothing is read at a data-dependent place.
+// Scalars of a steady-state iteration (with the previous vectors, zhat in the
+// ring's first entry) for timing the operator pass; the coefficients are zero,
+// so whatever the vectors hold, nothing is read at a data-dependent place.
 __global__ void k_tune_scalars(Scalars* sc, int batch) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= batch) return;
   Scalars v{};
-  v.state = ST_ACTIVE; v.pit = 4; v.it = 4; v.wmode = 2; v.zs = 1.0;
+  v.state = ST_ACTIVE; v.pit = kRing; v.it = kRing; v.zs = 1.0;
   sc[s] = v;
 }
 

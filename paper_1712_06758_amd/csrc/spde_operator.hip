@@ -1,14 +1,13 @@
-// Operator pass of the MINRES iteration (fused Lanczos recurrence, direction
-// and solution updates), one-cell-per-thread and column forms.
+// Operator pass of the MINRES iteration (fused Lanczos recurrence),
+// one-cell-per-thread and column forms.
 #include "spde_common.inc"
 
 namespace spde {
 
 // ---------------------------------------------------------------------------
 // operator pass of iteration j:
-//   v_{j+1} = A z_j - a_v v_j - b_v v_{j-1},  z_j = (P_sigma^-1 v_sigma, zhat_u) / gamma_j
-// and the delayed direction/solution update of step j-1.  One thread per
-// cell: the cell value and the three low faces of the cell.
+//   v_{j+1} = A z_j - a_v v_j - b_v v_{j-1},  z_j = (P_sigma^-1 v_sigma, zhat_u) / gamma_j.
+// One thread per cell: the cell value and the three low faces of the cell.
 //   (M z)_face = (M P_sigma^-1 v)_f / gamma              (line_terms)
 //   (B^T z_u)_face = h^2 (zhat[c - e_d] - zhat[c]) / gamma
 //   (A z)_cell = (h^2 q sum_d (z_hi - z_lo) / q - kappa^2 h^3 zhat) / gamma
@@ -24,7 +23,7 @@ __global__ __launch_bounds__(kBlock) void k_operator(Fields F, Box bx, int nb) {
   const int slot = lb / nb, blk = lb - slot * nb;
   const Scalars* S = F.sc + slot;
   const int state = S->state;
-  if (state != ST_ACTIVE && state != ST_FINISH) return;
+  if (state != ST_ACTIVE) return;
   const int j = S->pit;
   const int p = j & 1, pq = p ^ 1;
   const int64_t nc = bx.nc;
@@ -39,40 +38,17 @@ __global__ __launch_bounds__(kBlock) void k_operator(Fields F, Box bx, int nb) {
     k = __builtin_amdgcn_readfirstlane(k);
   }
   const int64_t co = cell_off(slot, nc);
-  const bool active = state == ST_ACTIVE;
   const bool has_prev = j > 1;
-  const int wm = S->wmode;
-  // x is written on even iterations and on the finishing pass; an odd
-  // iteration leaves its term to the next pass (coefficient xpend of W_{j-1})
-  const bool upd_x = wm >= 1 && ((j & 1) == 0 || state == ST_FINISH);
   const int idx[3] = {i, jj, k};
   const int64_t str[3] = {1, n, n2};
   // scalars before any store (after a store they could no longer be scalar loads)
   const double zs = S->zs, av = S->a_v, bv = S->b_v;
-  const double sww = S->ww, swwp = S->ww_prev, sxw = S->xw, sxp = S->xpend;
-  const bool acc = S->flags & FL_ACCUM;   // refinement pass: x holds the previous iterate
-
-  // Direction and solution updates (unnormalised directions, see Scalars):
-  //   W_{j+1} = zs zhat_j + ww W_j + ww_prev W_{j-1}      (W_j in w[pq], W_{j-1} in w[p])
-  //   x += xpend W_{j-1} + xw W_j                          (even passes, the finishing pass)
-  // The W store is unconditional (a pass without update writes back the old
-  // value) so that the loads it needs stay ahead of the other stores.
-  auto x_update = [&](double wj, double wjm1) {
-    if (upd_x) {
-      const double inc = sxp * wjm1 + sxw * wj;
-      F.x[co + c] = (j == 2 && !acc) ? inc : F.x[co + c] + inc;
-    }
-  };
-  if (!active) {   // the finishing pass only applies the last solution update
-    x_update(F.w[pq][co + c], wm >= 2 ? F.w[p][co + c] : 0.0);
-    return;
-  }
   // All loads first, unconditionally (the addresses are valid in every state;
   // values that a state does not need are discarded).  The stores go through
   // pointers that may alias the loads, so a load after a store, or inside a
   // branch the compiler may sink below the stores, would cost the wave another
   // memory round trip.
-  const TZ* z = reinterpret_cast<const TZ*>(F.z[p]) + co;
+  const TZ* z = reinterpret_cast<const TZ*>(F.z) + (j & F.zm) * F.zstr + co;
   double w[3][7], vo[3], zlo[3];
   const double zc = (double)z[c];
 #pragma unroll
@@ -84,7 +60,6 @@ __global__ __launch_bounds__(kBlock) void k_operator(Fields F, Box bx, int nb) {
     vo[d] = F.vs[pq][face_off(slot, d, nc) + c];
   }
   const double vuc = F.vu[p][co + c], vuo = F.vu[pq][co + c];
-  const double wj = F.w[pq][co + c], wjm1 = F.w[p][co + c];
   // VAR: cell-wise kappa (shared by the slots), read with the other loads
   const double kc = VAR ? bx.kap[c] : 0.0;
 
@@ -104,11 +79,6 @@ __global__ __launch_bounds__(kBlock) void k_operator(Fields F, Box bx, int nb) {
   const double Au = zs * (bx.h2q * dv - k2 * zc);
   const double nu = Au - av * vuc;
   F.vu[pq][co + c] = has_prev ? nu - bv * vuo : nu;
-  double wn = zs * zc;
-  if (wm >= 1) wn += sww * wj;
-  if (wm >= 2) wn += swwp * wjm1;
-  F.w[p][co + c] = wm >= 0 ? wn : wjm1;
-  if (wm >= 1) x_update(wj, wm >= 2 ? wjm1 : 0.0);
 }
 
 // Column form of the operator pass for n a multiple of 64.  A block owns
@@ -118,8 +88,8 @@ __global__ __launch_bounds__(kBlock) void k_operator(Fields F, Box bx, int nb) {
 // faces of its 4 rows (with a 3-face halo along x) and the y faces of rows
 // -3 .. +6 in LDS, from which the x and y windows are read.  Same arithmetic,
 // in the same order, as k_operator.
-// NT: the Lanczos, direction and solution vectors are streamed with the
-// nontemporal hint (chosen by the launcher from the launch's working set).
+// NT: the Lanczos vectors are streamed with the nontemporal hint (chosen by the
+// launcher from the launch's working set).
 template <typename TZ, int POLY, bool VAR, int ZC, bool NT>
 __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int nb) {
   constexpr int XW = 64 + 6, AXF = XW * 4, RXF = (AXF + kBlock - 1) / kBlock;   // x faces, halo 3 in x
@@ -130,7 +100,7 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
   const int slot = lb / nb, t = lb - slot * nb;
   const Scalars* S = F.sc + slot;
   const int state = S->state;
-  if (state != ST_ACTIVE && state != ST_FINISH) return;
+  if (state != ST_ACTIVE) return;
   const int j = S->pit;
   const int p = j & 1, pq = p ^ 1;
   const int64_t nc = bx.nc;
@@ -143,26 +113,8 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
   const int jj = __builtin_amdgcn_readfirstlane(y0 + wv);
   const int64_t col = i + (int64_t)n * jj;
   const int64_t co = cell_off(slot, nc);
-  const bool active = state == ST_ACTIVE;
   const bool has_prev = j > 1;
-  const int wm = S->wmode;
-  const bool upd_x = wm >= 1 && ((j & 1) == 0 || state == ST_FINISH);
   const double zs = S->zs, av = S->a_v, bv = S->b_v;
-  const double sww = S->ww, swwp = S->ww_prev, sxw = S->xw, sxp = S->xpend;
-  const bool acc = S->flags & FL_ACCUM;   // refinement pass: x holds the previous iterate
-  auto x_update = [&](int64_t c, double wj, double wjm1) {
-    if (upd_x) {
-      const double inc = sxp * wjm1 + sxw * wj;
-      st_stream<NT>((j == 2 && !acc) ? inc : ld_stream<NT>(&F.x[co + c]) + inc, &F.x[co + c]);
-    }
-  };
-  if (!active) {
-    for (int kk = 0; kk < ZC; ++kk) {
-      const int64_t c = col + n2 * (z0 + kk);
-      x_update(c, F.w[pq][co + c], wm >= 2 ? F.w[p][co + c] : 0.0);
-    }
-    return;
-  }
   // staged items: byte offset within a plane and the odd-reflection factor
   uint32_t xo[RXF], yo[RYF];
   double xf[RXF], yf[RYF];
@@ -184,7 +136,7 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
     yo[r] = q < AYF ? (uint32_t)(gx + n * min(src, n - 1)) * 8u : 0u;
     yf[r] = (q >= AYF || src == n) ? 0.0 : (neg ? -1.0 : 1.0);
   }
-  const TZ* z = reinterpret_cast<const TZ*>(F.z[p]) + co;
+  const TZ* z = reinterpret_cast<const TZ*>(F.z) + (j & F.zm) * F.zstr + co;
   const double* vs0 = F.vs[p] + face_off(slot, 0, nc);
   const double* vs1 = F.vs[p] + face_off(slot, 1, nc);
   const double* vz = F.vs[p] + face_off(slot, 2, nc) + col;
@@ -226,7 +178,6 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
 #pragma unroll
     for (int d = 0; d < 3; ++d) vo[d] = ld_stream<NT>(&F.vs[pq][face_off(slot, d, nc) + c]);
     const double vuc = ld_stream<NT>(&F.vu[p][co + c]), vuo = ld_stream<NT>(&F.vu[pq][co + c]);
-    const double wj = ld_stream<NT>(&F.w[pq][co + c]), wjm1 = ld_stream<NT>(&F.w[p][co + c]);
     const double kc = VAR ? bx.kap[c] : 0.0;
     __syncthreads();
     double w[2][7];
@@ -253,11 +204,6 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
     const double Au = zs * (bx.h2q * dv - k2 * zc);
     const double nu = Au - av * vuc;
     st_stream<NT>(has_prev ? nu - bv * vuo : nu, &F.vu[pq][co + c]);
-    double wn = zs * zc;
-    if (wm >= 1) wn += sww * wj;
-    if (wm >= 2) wn += swwp * wjm1;
-    st_stream<NT>(wm >= 0 ? wn : wjm1, &F.w[p][co + c]);
-    if (wm >= 1) x_update(c, wj, wm >= 2 ? wjm1 : 0.0);
 #pragma unroll
     for (int q = 0; q < 6; ++q) wz[q] = wz[q + 1];
     zprev = zc;
@@ -267,19 +213,12 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
 
 // planes per block of the column form of the operator pass
 constexpr int kOpZC = 16;
-// The column pass streams its vectors with the nontemporal hint when the
-// launch's vectors (about 128 bytes per cell and sample) exceed this size.
-// MI355X has a 256 MB last-level cache: one 128^3 sample (about 265 MB) still
-// runs faster without the hint (its vectors largely stay cached between
-// passes), two or more run faster with it.
-constexpr double kOpStreamBytes = 384.0 * 1024 * 1024;
-
 hipError_t launch_operator(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st) {
   if (bx.n % 64 == 0 && bx.n % kOpZC == 0) {
     // 64 x 4 columns of kOpZC planes per block
     const int nbc = (bx.n / 64) * (bx.n / 4) * (bx.n / kOpZC);
     const dim3 gridc(nbc * batch), blkc(kBlock);
-    const bool nt = 128.0 * (double)bx.nc * (double)batch > kOpStreamBytes;
+    const bool nt = streams_past_cache(bx, batch);
 #define SPDE_OPC(TZ, NT)                                                                                        \
   do {                                                                                                          \
     if (bx.kap) {                                                                                               \
