@@ -105,3 +105,45 @@ def test_sampling_with_device_transfer(torch_cuda):
         box.set_mesh(xyz, tets, builder=builder)
         outs.append(box.sample(xi)["u_tet"].cpu().numpy())
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("n,m,count", [
+    (2, 3, 1), (7, 4, 63), (16, 5, 65),       # one wave and its edges; n that is no power of two
+    (64, 9, 4096), (33, 9, 4097), (8, 9, 4374),   # one scan tile, and one row more
+    (24, 2, 48), (20, 1, 6), (32, 1, 6),      # tets far wider than a cell
+    (16, 28, 131712),                         # several tets per lane
+])
+def test_device_transfer_sizes_match_host(torch_cuda, n, m, count):
+    """Bit for bit the host clipper's matrix at the edges of waves, scan tiles
+    and work per lane, and for tets far smaller and far larger than a cell."""
+    xyz, tets = tet_mesh(0.2, 0.8, m, seed=m)
+    tets = np.ascontiguousarray(tets[:count])
+    say(f"device transfer n={n} m={m} {tets.shape[0]} tets")
+    rp, ci, cv = device_csr(torch_cuda, n, xyz, tets)
+    if n & (n - 1) or n < 4:      # the host builder takes powers of two: the oracle's rows instead
+        np.testing.assert_allclose(np.add.reduceat(cv, rp[:-1]), 1.0, atol=1e-12)
+        for r in np.random.default_rng(3).choice(tets.shape[0], min(4, tets.shape[0]), replace=False):
+            c_or, v_or = T.tet_row(xyz, tets[r], n)
+            got = dict(zip(ci[rp[r]:rp[r + 1]].tolist(), cv[rp[r]:rp[r + 1]].tolist()))
+            ref = dict(zip(c_or.tolist(), v_or.tolist()))
+            for k in set(got) | set(ref):
+                assert abs(got.get(k, 0.0) - ref.get(k, 0.0)) <= 1e-12, (r, k)
+        return
+    rh, ch, vh = P().build_transfer_host(n, xyz, tets)
+    assert np.array_equal(rp, rh) and np.array_equal(ci, ch)
+    assert np.array_equal(cv.view(np.uint64), vh.view(np.uint64))
+
+
+def test_device_transfer_names_the_first_invalid_tet_of_many(torch_cuda):
+    """The row scan works in tiles: an invalid tet of a later tile is found, and
+    of several the first."""
+    PP = P()
+    xyz, tets = tet_mesh(0.2, 0.8, 12)
+    say("device transfer invalid tets in later tiles")
+    for rows in ((9000,), (10367,), (4096, 8200), (4095, 4097)):
+        bad = tets.copy()
+        for r in rows:
+            bad[r, 1] = -1
+        with pytest.raises(PP.SpdeError) as ei:
+            PP.build_transfer_device(16, xyz, bad)
+        assert f"tet {rows[0]} " in str(ei.value), str(ei.value)
