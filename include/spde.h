@@ -522,7 +522,9 @@ spde_status spde_set_poll_interval(spde_handle h, int iters);
  *               0, 3, 6, ... run on their own, bracketed by an event pair,
  *               and everything between them replays as captured graphs.
  *   enable = 0 stops and keeps the totals; -1 clears the totals (the mode
- *   is kept). */
+ *   is kept).
+ * Boxes of 8^3 and 16^3 with constant kappa run whole iterations in one launch
+ * (class iterations_small, recorded in mode 1). */
 spde_status spde_timing(spde_handle h, int enable);
 int         spde_kernel_count(void);
 const char* spde_kernel_name(int id);

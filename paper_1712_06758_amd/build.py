@@ -18,7 +18,7 @@ ARCH = os.environ.get("SPDE_OFFLOAD_ARCH", "gfx950")
 
 # the multigrid kernels of each level precision and the operator pass are
 # translation units of their own, so that they compile side by side
-SOURCES = ["spde_kernels.hip", "spde_operator.hip", "spde_mg_f32.hip", "spde_mg_f64.hip", "spde.cpp",
+SOURCES = ["spde_kernels.hip", "spde_operator.hip", "spde_small.hip", "spde_mg_f32.hip", "spde_mg_f64.hip", "spde.cpp",
            "transfer_build.cpp"]
 
 FLAGS = [

@@ -55,7 +55,8 @@ spde_status fail(spde_status s, const char* fmt, ...) {
 
 const char* kKernelNames[KID_COUNT] = {
     "init", "mg_down_fine", "mg_down", "mg_coarse", "mg_up", "mg_up_fine",
-    "scalar", "operator", "output", "flux", "resid", "spmm", "restrict_noise", "spmm_stage", "direction"};
+    "scalar", "operator", "output", "flux", "resid", "spmm", "restrict_noise", "spmm_stage", "direction",
+    "iterations_small"};
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -305,6 +306,9 @@ double slot_bytes(const Ctx* c, int kid, int level, int iter) {
       // `level` iterations up to `iter`: read their zhat, W twice and x (none of them before the first
       // pass of a solve); write W twice and x
       return nc * ((double)level * sz + (iter > level ? 24.0 : 0.0) + 24.0);
+    case KID_SMALL:
+      // `level` iterations: v_j and v_{j-1} read and written once, zhat of each written
+      return nc * (128.0 + (double)level * sz);
     case KID_MG_UP_FINE: return nc * (8.0 + sz / 8.0 + 24.0 + sz + (c->box.kap ? 8.0 : 0.0));
     case KID_MG_DOWN_FINE: return nc * (8.0 + sz / 8.0);
     case KID_MG_DOWN: { const double m = (double)c->lv[level].nc; return m * (sz + sz / 8.0); }
@@ -477,6 +481,13 @@ constexpr int kTimedStride = 3;
 // between them replays as graphs.
 spde_status enqueue_chunk(Ctx* c, const View& V, int batch, hipStream_t st, bool graphs, bool whole, int iter0,
                           int count) {
+  if (small_box(c->box, c->lv[0])) {
+    // whole iterations in one launch, timed as a class of their own
+    if (c->cinv_dirty) return fail(SPDE_EINVAL, "the exact 4^3 coarse solve was not prepared before the iterations");
+    Timed t(c, KID_SMALL, iter0 + 1, st, count, V.s0, batch);
+    HIPCHK(launch_small(c->fp64(), V.F, c->box, c->lv[0], c->lv[1], c->cinv, batch, count, st));
+    return SPDE_OK;
+  }
   if (graphs && c->timing == 2) {
     bool ok = launch_graph(c, V, batch, st, 1);   // V-part of iteration 0
     for (int k = 0; ok && k < count; k += kTimedStride) {
@@ -555,6 +566,9 @@ void close_timing(Ctx* c, int batch) {
       } else if (r.kid == KID_DIRECTION) {
         const int last = std::min(r.iter, J + 1), m = last - (r.iter - r.level);
         if (m > 0) bytes += slot_bytes(c, r.kid, m, last);
+      } else if (r.kid == KID_SMALL) {
+        const int m = std::min(r.iter + r.level - 1, J + 1) - r.iter + 1;
+        if (m > 0) bytes += slot_bytes(c, r.kid, m, r.iter);
       } else if (r.iter >= 1 && r.iter <= J + 1) {
         bytes += slot_bytes(c, r.kid, r.level, r.iter);
       }
@@ -1184,13 +1198,15 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
   // carried through idle iterations (a batch that needs fewer finds its samples
   // done, and every kernel leaves at once).  Polls held up a 16^3 call, whose
   // iterations take 33 us, by 70 us in all.
+  const bool small = small_box(bx, c->lv[0]);
   auto iterate = [&](int expect, int& launched) -> spde_status {
     launched = 0;
     const int cap = c->max_iter + 2;
     bool all_done = false;
     while (!all_done && launched < cap + c->poll) {
       int count = c->poll;
-      if (expect > launched) count = std::min(count, expect - launched);
+      // (the small boxes, whose launches take whole iterations, as one block)
+      if (expect > launched) count = small ? expect - launched : std::min(count, expect - launched);
       int waiting = c->unapplied;   // the same for both halves
       if (split) {
         int w1 = waiting;

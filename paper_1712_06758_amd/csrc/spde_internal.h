@@ -46,7 +46,7 @@ struct alignas(16) Scalars {
   double zs;                  // 1 / gamma_j
   double a_v;                 // delta_j / gamma_j
   double b_v;                 // gamma_j / gamma_{j-1}
-  double al1_prev;            // alpha1 of the previous Givens step
+  double ral1_prev;           // 1 / alpha1 of the previous Givens step
   double tol;                 // relative stopping tolerance on |eta| / eta0
   int it;                     // iteration the V-cycle and the scalar step work on
   int pit;                    // iteration the operator pass works on
@@ -196,7 +196,7 @@ __host__ __device__ inline int64_t face_off(int slot, int d, int64_t nc) { retur
 enum KernelId : int {
   KID_INIT = 0, KID_MG_DOWN_FINE, KID_MG_DOWN, KID_MG_COARSE, KID_MG_UP, KID_MG_UP_FINE,
   KID_SCALAR, KID_OPERATOR, KID_OUTPUT, KID_FLUX, KID_RESID, KID_SPMM, KID_RESTRICT, KID_SPMM_STAGE,
-  KID_DIRECTION, KID_COUNT
+  KID_DIRECTION, KID_SMALL, KID_COUNT
 };
 
 }  // namespace spde
@@ -258,6 +258,12 @@ hipError_t launch_mg_coarse(bool fp64, const void* btop, void* etop, const Coars
 hipError_t launch_coarse_inverse(bool fp64, const Level& L, void* out, hipStream_t st);
 hipError_t launch_scalar(const Fields& F, int nb_up, int nb_pb, int batch, hipStream_t st);
 hipError_t launch_operator(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st);
+// Whole iterations of an 8^3 or 16^3 box with constant kappa in one launch
+// (small_box: whether the box and its finest level are such): up to the ring's
+// entries, everything but the direction pass.
+bool small_box(const Box& bx, const Level& top);
+hipError_t launch_small(bool fp64, const Fields& F, const Box& bx, const Level& top, const Level& next,
+                        const void* cinv, int batch, int iters, hipStream_t st);
 // Apply the waiting direction and solution updates of the slots (a slot with
 // none is left as it is).
 hipError_t launch_direction(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st);

@@ -23,6 +23,7 @@
 #include <mutex>
 
 #include "spde_common.inc"
+#include "spde_scalar.inc"
 
 namespace spde {
 
@@ -92,57 +93,10 @@ __global__ __launch_bounds__(kBlock) void k_scalar(Fields F, int nb_up, int nb_p
   (void)nb_pb;
 
   Scalars s = *S;
-  const double gg = a0;               // gamma_j^2
-  if (!(gg >= 0.0) || !isfinite(gg) || !isfinite(a1)) {
-    s.state = ST_FAILED; s.iters = j - 1; *S = s; return;
-  }
-  if (gg == 0.0 && j == 1) {           // zero right-hand side: the solution is 0
-    s.state = ST_DONE; s.flags |= FL_ZERO; s.iters = 0; *S = s; return;
-  }
-  const double gam = sqrt(gg);
-  const double del = gg > 0.0 ? a1 / gg : 0.0;
   DirCoef dc{};
-  if (j == 1) {
-    s.eta = gam; s.eta0 = gam;
-    s.c = s.c_prev = 1.0; s.s = s.s_prev = 0.0;
-    s.al1_prev = 1.0;                  // W_2 = z_1
-    s.b_v = 0.0;
-  } else {
-    // complete the Givens rotation of step j-1 now that gamma_j is known
-    const double dp = s.delta, gp = s.gamma;
-    const double al0 = s.c * dp - s.c_prev * s.s * gp;
-    const double al1 = sqrt(al0 * al0 + gg);
-    if (!(al1 > 0.0) || !isfinite(al1)) { s.state = ST_FAILED; s.iters = j - 1; *S = s; return; }
-    const double cn = al0 / al1, sn = gam / al1;
-    // x_{j-1} = x_{j-2} + c_j eta w_j with w_j = W_j / alpha1_{j-1}
-    dc.xw = cn * s.eta / al1;
-    s.eta = -sn * s.eta;
-    // W_{j+1} = z_j - alpha3_j w_{j-1} - alpha2_j w_j, with
-    // alpha2_j = s_j delta_j + c_{j-1} c_j gamma_j and alpha3_j = s_{j-1} gamma_j
-    const double a2 = sn * del + s.c * cn * gam;
-    const double a3 = s.s * gam;
-    dc.ww = -a2 / al1;
-    dc.ww_prev = j > 2 ? -a3 / s.al1_prev : 0.0;
-    s.al1_prev = al1;
-    s.c_prev = s.c; s.s_prev = s.s;
-    s.c = cn; s.s = sn;
-    s.b_v = gam / gp;
-    if (fabs(s.eta) <= s.tol * s.eta0 || gg == 0.0) {
-      s.state = ST_DONE; s.iters = j - 1;
-    } else if (j - 1 >= s.max_iter) {
-      s.state = ST_DONE; s.iters = j - 1; s.flags |= FL_NOTCONV;
-    }
-  }
-  s.gamma_prev = (j == 1) ? 1.0 : s.gamma;
-  s.gamma = gam;
-  s.delta = del;
-  s.zs = gam > 0.0 ? 1.0 / gam : 0.0;
-  s.a_v = gam > 0.0 ? del / gam : 0.0;
-  s.pit = j;
-  s.it = j + 1;
+  const bool stored = scalar_step(s, a0, a1, dc);
   *S = s;
-  dc.zs = s.zs;
-  F.dir[(int64_t)slot * (F.zm + 1) + (j & F.zm)] = dc;
+  if (stored) F.dir[(int64_t)slot * (F.zm + 1) + (j & F.zm)] = dc;
 }
 
 // ---------------------------------------------------------------------------
