@@ -12,12 +12,10 @@ namespace spde {
 //   (B^T z_u)_face = h^2 (zhat[c - e_d] - zhat[c]) / gamma
 //   (A z)_cell = (h^2 q sum_d (z_hi - z_lo) / q - kappa^2 h^3 zhat) / gamma
 
-// UNI: every wave lies in one grid row (n >= 64), so the y and z line
-// positions, and with them the y- and z-window offsets, are wave-uniform.
 // POLY: face block of the preconditioner (0 diag(M)^-1, 1 Neumann series), a
 // template parameter so that no window load sits behind a branch on it.
 // VAR: cell-wise kappa (the reaction term kappa_c^2 h^3 of the cell row).
-template <typename TZ, bool UNI, int POLY, bool VAR>
+template <typename TZ, int POLY, bool VAR>
 __global__ __launch_bounds__(kBlock) void k_operator(Fields F, Box bx, int nb) {
   const int lb = xcd_remap(blockIdx.x, gridDim.x);
   const int slot = lb / nb, blk = lb - slot * nb;
@@ -32,11 +30,7 @@ __global__ __launch_bounds__(kBlock) void k_operator(Fields F, Box bx, int nb) {
   const int64_t c = (int64_t)blk * kBlock + threadIdx.x;
   if (c >= nc) return;
   const int i = (int)(c % n);
-  int jj = (int)((c / n) % n), k = (int)(c / n2);
-  if constexpr (UNI) {
-    jj = __builtin_amdgcn_readfirstlane(jj);
-    k = __builtin_amdgcn_readfirstlane(k);
-  }
+  const int jj = (int)((c / n) % n), k = (int)(c / n2);
   const int64_t co = cell_off(slot, nc);
   const bool has_prev = j > 1;
   const int idx[3] = {i, jj, k};
@@ -211,54 +205,56 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
 }
 
 
-// planes per block of the column form of the operator pass
-constexpr int kOpZC = 16;
+// Planes per block of the column form.  A launch whose vectors stream past the
+// last-level cache has thousands of blocks and takes 16: deeper blocks read fewer
+// planes of the z windows twice (128^3 x 2 mixed, a call: 7.82 ms with 16, 7.94
+// with 4; 256^3 x 1: 25.9 and 26.2).  A launch that stays in the cache has few
+// blocks, each a chain of one memory latency per plane, and takes 4, or 2 where
+// 4 would leave fewer than four blocks per compute unit (64^3 x 1 mixed, a call:
+// 2.77 ms with 16, 2.12 with 4, 2.06 with 2; 64^3 x 7: 5.08, 4.85, 4.86; 128^3 x 1
+// float64: 7.42, 7.24, 7.26).
+constexpr int kOpZC = 16, kOpZCShort = 4, kOpZCShortest = 2;
+
+template <typename TZ, int ZC, bool NT>
+static hipError_t launch_operator_col(const Fields& F, const Box& bx, int batch, hipStream_t st) {
+  const int nb = (bx.n / 64) * (bx.n / 4) * (bx.n / ZC);   // 64 x 4 columns of ZC planes per block
+  const dim3 grid(nb * batch), blk(kBlock);
+  if (bx.kap) {
+    if (bx.poly) hipLaunchKernelGGL((k_operator_col<TZ, 1, true, ZC, NT>), grid, blk, 0, st, F, bx, nb);
+    else hipLaunchKernelGGL((k_operator_col<TZ, 0, true, ZC, NT>), grid, blk, 0, st, F, bx, nb);
+  } else {
+    if (bx.poly) hipLaunchKernelGGL((k_operator_col<TZ, 1, false, ZC, NT>), grid, blk, 0, st, F, bx, nb);
+    else hipLaunchKernelGGL((k_operator_col<TZ, 0, false, ZC, NT>), grid, blk, 0, st, F, bx, nb);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_operator(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st) {
-  if (bx.n % 64 == 0 && bx.n % kOpZC == 0) {
-    // 64 x 4 columns of kOpZC planes per block
-    const int nbc = (bx.n / 64) * (bx.n / 4) * (bx.n / kOpZC);
-    const dim3 gridc(nbc * batch), blkc(kBlock);
-    const bool nt = streams_past_cache(bx, batch);
-#define SPDE_OPC(TZ, NT)                                                                                        \
-  do {                                                                                                          \
-    if (bx.kap) {                                                                                               \
-      if (bx.poly) hipLaunchKernelGGL((k_operator_col<TZ, 1, true, kOpZC, NT>), gridc, blkc, 0, st, F, bx, nbc);  \
-      else hipLaunchKernelGGL((k_operator_col<TZ, 0, true, kOpZC, NT>), gridc, blkc, 0, st, F, bx, nbc);          \
-    } else {                                                                                                    \
-      if (bx.poly) hipLaunchKernelGGL((k_operator_col<TZ, 1, false, kOpZC, NT>), gridc, blkc, 0, st, F, bx, nbc); \
-      else hipLaunchKernelGGL((k_operator_col<TZ, 0, false, kOpZC, NT>), gridc, blkc, 0, st, F, bx, nbc);         \
-    }                                                                                                           \
-  } while (0)
-    if (z_fp64) {
-      if (nt) SPDE_OPC(double, true);
-      else SPDE_OPC(double, false);
-    } else {
-      if (nt) SPDE_OPC(float, true);
-      else SPDE_OPC(float, false);
-    }
-#undef SPDE_OPC
-    return hipGetLastError();
+  if (bx.n % 64 == 0) {
+    if (streams_past_cache(bx, batch))
+      return z_fp64 ? launch_operator_col<double, kOpZC, true>(F, bx, batch, st)
+                    : launch_operator_col<float, kOpZC, true>(F, bx, batch, st);
+    // (a block of 4 planes has 1024 cells)
+    if ((double)bx.nc * batch >= 4.0 * 256 * 1024)
+      return z_fp64 ? launch_operator_col<double, kOpZCShort, false>(F, bx, batch, st)
+                    : launch_operator_col<float, kOpZCShort, false>(F, bx, batch, st);
+    return z_fp64 ? launch_operator_col<double, kOpZCShortest, false>(F, bx, batch, st)
+                  : launch_operator_col<float, kOpZCShortest, false>(F, bx, batch, st);
   }
   const int nb = operator_blocks(bx);
   const dim3 grid(nb * batch), blk(kBlock);
-  // with n >= 64 every 64-lane wave lies in one grid row
-#define SPDE_OP(TZ, UNI)                                                                             \
-  do {                                                                                               \
-    if (bx.kap) {                                                                                    \
-      if (bx.poly) hipLaunchKernelGGL((k_operator<TZ, UNI, 1, true>), grid, blk, 0, st, F, bx, nb);  \
-      else hipLaunchKernelGGL((k_operator<TZ, UNI, 0, true>), grid, blk, 0, st, F, bx, nb);          \
-    } else {                                                                                         \
-      if (bx.poly) hipLaunchKernelGGL((k_operator<TZ, UNI, 1, false>), grid, blk, 0, st, F, bx, nb); \
-      else hipLaunchKernelGGL((k_operator<TZ, UNI, 0, false>), grid, blk, 0, st, F, bx, nb);         \
-    }                                                                                                \
+#define SPDE_OP(TZ)                                                                             \
+  do {                                                                                          \
+    if (bx.kap) {                                                                               \
+      if (bx.poly) hipLaunchKernelGGL((k_operator<TZ, 1, true>), grid, blk, 0, st, F, bx, nb);  \
+      else hipLaunchKernelGGL((k_operator<TZ, 0, true>), grid, blk, 0, st, F, bx, nb);          \
+    } else {                                                                                    \
+      if (bx.poly) hipLaunchKernelGGL((k_operator<TZ, 1, false>), grid, blk, 0, st, F, bx, nb); \
+      else hipLaunchKernelGGL((k_operator<TZ, 0, false>), grid, blk, 0, st, F, bx, nb);         \
+    }                                                                                           \
   } while (0)
-  if (bx.n >= 64) {
-    if (z_fp64) SPDE_OP(double, true);
-    else SPDE_OP(float, true);
-  } else {
-    if (z_fp64) SPDE_OP(double, false);
-    else SPDE_OP(float, false);
-  }
+  if (z_fp64) SPDE_OP(double);
+  else SPDE_OP(float);
 #undef SPDE_OP
   return hipGetLastError();
 }

@@ -79,3 +79,22 @@ def test_captured_slot_steps_replay():
             g.replay()
         st.synchronize()
     assert torch.equal(finish(), want)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_operator_blocks_of_every_depth_agree(precision, kind):
+    """The operator pass takes blocks of 2, 4 or 16 planes by the size of the
+    launch (64^3: 1, 4 and 13 samples); a sample's result is the same bit for bit."""
+    torch, P = _setup()
+    say(f"operator block depths {precision} face block {kind}")
+    n = 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    xs = torch.randn(13, 3 * n * n * (n + 1), generator=g, device="cuda", dtype=torch.float64)
+    xu = torch.randn(13, n ** 3, generator=g, device="cuda", dtype=torch.float64)
+    box = P.Box(n, 10.0, precision=precision, max_batch=13)
+    box.set_face_preconditioner(kind)
+    ys, yu = box.apply_operator_precond(xs, xu)
+    for b in (1, 4):
+        s, u = box.apply_operator_precond(xs[:b].contiguous(), xu[:b].contiguous())
+        assert torch.equal(s, ys[:b]) and torch.equal(u, yu[:b]), b
