@@ -437,7 +437,8 @@ spde_status enqueue_iteration(Ctx* c, const View& V, int batch, hipStream_t st, 
 // with a V-part).  The iteration numbers inside a graph are irrelevant: the
 // kernels take their state from the per-slot scalars.
 spde_status get_graph(Ctx* c, const View& V, int batch, hipStream_t st, hipGraphExec_t* out, int L) {
-  const int64_t key = ((int64_t)V.s0 << 40) | ((int64_t)L << 24) | (int64_t)batch;
+  const int64_t key =
+      ((int64_t)V.F.spread << 60) | ((int64_t)V.s0 << 40) | ((int64_t)L << 24) | (int64_t)batch;
   auto it = c->graphs.find(key);
   if (it != c->graphs.end()) { *out = it->second; return SPDE_OK; }
   hipGraph_t g = nullptr;
@@ -1463,7 +1464,8 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = pick_stream(c, stream);
   const bool graphs = c->use_graphs && c->timing != 1 && st != nullptr;
-  const View V0 = make_view(c, 0);
+  View V0 = make_view(c, 0);
+  V0.F.spread = 1;
   // A caller may be capturing the stream and replay these launches any number
   // of times: the direction passes are then part of what is captured, with
   // nothing left waiting before or after.

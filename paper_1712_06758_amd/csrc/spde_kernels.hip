@@ -118,8 +118,8 @@ template <typename TZ, bool NT>
 __global__ __launch_bounds__(kBlock) void k_direction(Fields F, int64_t nc, int nb) {
   using VZ = typename ZVec<TZ>::type;
   constexpr int V = 16 / sizeof(TZ), H = V / 2;   // cells per thread, double pairs per thread
-  const int lb = xcd_remap(blockIdx.x, gridDim.x);
-  const int slot = lb / nb, blk = lb - slot * nb;
+  int slot, blk;
+  slot_block(blockIdx.x, gridDim.x, nb, slot, blk);
   Scalars* S = F.sc + slot;
   const int state = S->state;
   if (state != ST_ACTIVE && state != ST_DONE) return;

@@ -98,3 +98,18 @@ def test_operator_blocks_of_every_depth_agree(precision, kind):
     for b in (1, 4):
         s, u = box.apply_operator_precond(xs[:b].contiguous(), xu[:b].contiguous())
         assert torch.equal(s, ys[:b]) and torch.equal(u, yu[:b]), b
+
+
+@pytest.mark.parametrize("n", [32, 64])
+def test_samples_keep_their_bits_in_every_block_order(n):
+    """Blocks are dealt out to the XCDs by slot, in turns of eight and a remainder:
+    every sample of batches around those edges is what it is alone."""
+    torch, P = _setup()
+    say(f"block orders n={n}")
+    xi = torch.randn(17, n ** 3, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda",
+                     dtype=torch.float64)
+    box = P.Box(n, 10.0, precision="mixed", max_batch=17)
+    want = box.sample(xi, u_box=True)["u_box"]
+    for b in (7, 8, 9, 16):
+        assert torch.equal(box.sample(xi[:b].contiguous(), u_box=True)["u_box"], want[:b]), b
+    assert torch.equal(box.sample(xi[16:].contiguous(), u_box=True)["u_box"][0], want[16])
