@@ -106,6 +106,31 @@ template <typename T>
 __device__ __forceinline__ T ld_off(const T* base, uint32_t byte_off) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte_off);
 }
+// A wave-uniform pointer that the compiler may not take apart.  Left to itself
+// it adds each lane's offset to the array's start once and the uniform plane
+// offset to that 64-bit sum at every load: an instruction per load and a
+// register pair per offset that the scalar base of the load does without.
+template <typename T>
+using GlobalPtr = __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> scalar_base(T* p) {
+  uint64_t u = reinterpret_cast<uint64_t>(p);
+  asm("" : "+s"(u));
+  return reinterpret_cast<GlobalPtr<T>>(u);
+}
+template <typename T>
+__device__ __forceinline__ T ld_off(GlobalPtr<const T> base, uint32_t byte_off) {
+  return *reinterpret_cast<GlobalPtr<const T>>(reinterpret_cast<GlobalPtr<const char>>(base) + byte_off);
+}
+template <typename T>
+__device__ __forceinline__ void st_off(T v, GlobalPtr<T> base, uint32_t byte_off) {
+  *reinterpret_cast<GlobalPtr<T>>(reinterpret_cast<GlobalPtr<char>>(base) + byte_off) = v;
+}
+// Sign of x flipped where bit `bit` of `mask` is set.
+__device__ __forceinline__ double flip_sign(double x, uint32_t mask, int bit) {
+  const int hi = __double2hiint(x) ^ (int)((mask << (31 - bit)) & 0x80000000u);
+  return __hiloint2double(hi, __double2loint(x));
+}
 // Streaming accesses for vectors that a pass reads once and writes once.  With
 // NT they carry the nontemporal hint: at sizes far beyond the caches the lines
 // they bring in then need not displace the ones that other streams of the pass
