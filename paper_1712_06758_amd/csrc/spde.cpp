@@ -90,7 +90,6 @@ struct Ctx {
   int nlev = 0;                 // levels 0..nlev-1 (m = n >> l, down to 1)
   Level lv[kMaxLevels];
   int top = 1;                  // first level handled by the persistent kernel
-  size_t coarse_lds = 0;
   CoarseParams cp{};
   int shape_down[kMaxLevels];
   int shape_up[kMaxLevels];
@@ -186,31 +185,17 @@ void set_level(Level& L, int m, double kappa) {
 // 4^3 or larger.
 bool coarse_dense(const Ctx* c) { return c->lv[c->top].m >= 4; }
 
-size_t coarse_bytes(const Ctx* c, int top) {
-  size_t tot = 0;
-  for (int l = top; l < c->nlev; ++l) tot += 4 * (size_t)c->lv[l].nc * c->szm();
-  return tot;
-}
-
 void plan_hierarchy(Ctx* c) {
   c->nlev = 0;
   for (int m = c->n; m >= 1; m >>= 1) set_level(c->lv[c->nlev++], m, c->kappa_pre);
   c->mg_dirty = c->mg_cellwise;   // level diagonals (if any) are rebuilt before the next solve
   c->cinv_dirty = true;
-  // persistent kernel: the largest levels (below the finest) that fit in LDS, at most 16^3
-  int top = c->nlev - 1;
-  for (int l = 1; l < c->nlev; ++l) {
-    if (c->lv[l].m <= 16 && coarse_bytes(c, l) + kCoarseStaticLds <= (size_t)c->lds_limit) { top = l; break; }
-  }
+  // persistent kernel: the levels below the finest from 16^3 down
+  int top = std::min(1, c->nlev - 1);
+  while (c->lv[top].m > 16) ++top;
   c->top = top;
-  c->coarse_lds = coarse_bytes(c, top);
   c->cp.nl = c->nlev - top;
-  int64_t off = 0;
-  for (int l = top; l < c->nlev; ++l) {
-    c->cp.lv[l - top] = c->lv[l];
-    c->cp.off[l - top] = off;
-    off += 4 * c->lv[l].nc;
-  }
+  for (int l = top; l < c->nlev; ++l) c->cp.lv[l - top] = c->lv[l];
   for (int l = 0; l < c->nlev; ++l) {
     c->shape_down[l] = 0;
     c->shape_up[l] = c->fp64() ? 1 : 0;
@@ -380,7 +365,7 @@ spde_status enqueue_vcycle(Ctx* c, const View& V, int batch, hipStream_t st, int
     return fail(SPDE_EINVAL, "the exact 4^3 coarse solve was not prepared before the V-cycle");
   {
     Timed t(c, KID_MG_COARSE, iter, st, 0, s0, batch);
-    HIPCHK(launch_mg_coarse(f64, V.mgb[c->top], V.mge[c->top], c->cp, c->coarse_lds, batch, sc, st));
+    HIPCHK(launch_mg_coarse(f64, V.mgb[c->top], V.mge[c->top], c->cp, batch, sc, st));
   }
   for (int l = c->top - 1; l >= 1; --l) {
     Timed t(c, KID_MG_UP, iter, st, l, s0, batch);
@@ -943,7 +928,6 @@ spde_status spde_bind_workspace(spde_handle h, void* dev_ptr, size_t bytes) {
   c->slots_hi = 0;
   c->ws = (char*)dev_ptr;
   c->ws_bytes = bytes;
-  HIPCHK(prepare_coarse(c->fp64(), c->coarse_lds));
   return SPDE_OK;
 }
 

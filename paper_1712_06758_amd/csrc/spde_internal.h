@@ -14,8 +14,6 @@
 namespace spde {
 
 constexpr int kMaxLevels = 12;
-// static LDS of the persistent coarse kernel (a table of 8 reciprocals per level)
-constexpr size_t kCoarseStaticLds = kMaxLevels * 8 * sizeof(double);
 constexpr int kBlock = 256;          // threads per block of the streaming kernels
 
 // Per-sample solver state (one per batch slot).
@@ -192,7 +190,6 @@ struct Level {
 struct CoarseParams {
   int nl;                      // levels handled (top first, last is 1^3 or the coarsest)
   Level lv[kMaxLevels];
-  int64_t off[kMaxLevels];     // element offset of each level's 4 arrays in LDS
   const void* cinv;            // 64 x 64 inverse of the 4^3 level's operator (level precision),
                                // row-major; read when the top level is 4^3 or larger
 };
@@ -261,7 +258,6 @@ hipError_t launch_mg_down(bool fp64, int shape, bool fine, const void* b0, const
 hipError_t launch_mg_up(bool fp64, int shape, bool fine, const void* b0, const void* b1, const void* eH, void* o,
                         int64_t ostr, int om, const Level& L, int batch, const Scalars* sc, const double* vs0,
                         const double* vs1, double* part, const Box& bx, hipStream_t st);
-hipError_t prepare_coarse(bool fp64, size_t lds_bytes);
 // the same per level precision (spde_mg_f32.hip / spde_mg_f64.hip)
 #define SPDE_MG_DECL(NAME)                                                                                      \
   hipError_t launch_mg_down_##NAME(int shape, bool fine, const void* b0, const void* b1, void* rH,            \
@@ -271,15 +267,14 @@ hipError_t prepare_coarse(bool fp64, size_t lds_bytes);
                                  const Scalars* sc,                                                           \
                                  const double* vs0, const double* vs1, double* part, const Box& bx,           \
                                  hipStream_t st);                                                             \
-  hipError_t prepare_coarse_##NAME(size_t lds_bytes);                                                         \
-  hipError_t launch_mg_coarse_##NAME(const void* btop, void* etop, const CoarseParams& P, size_t lds_bytes,   \
-                                     int batch, const Scalars* sc, hipStream_t st);                          \
+  hipError_t launch_mg_coarse_##NAME(const void* btop, void* etop, const CoarseParams& P, int batch,          \
+                                     const Scalars* sc, hipStream_t st);                                     \
   hipError_t launch_coarse_inverse_##NAME(const Level& L, void* out, hipStream_t st);
 SPDE_MG_DECL(f32)
 SPDE_MG_DECL(f64)
 #undef SPDE_MG_DECL
-hipError_t launch_mg_coarse(bool fp64, const void* btop, void* etop, const CoarseParams& P, size_t lds_bytes,
-                            int batch, const Scalars* sc, hipStream_t st);
+hipError_t launch_mg_coarse(bool fp64, const void* btop, void* etop, const CoarseParams& P, int batch,
+                            const Scalars* sc, hipStream_t st);
 // Inverse of the 4^3 level's operator S~ (L.m must be 4) into out (64 x 64, level precision).
 hipError_t launch_coarse_inverse(bool fp64, const Level& L, void* out, hipStream_t st);
 hipError_t launch_scalar(const Fields& F, int nb_up, int nb_pb, int batch, hipStream_t st);

@@ -17,6 +17,7 @@
 // that the direction pass follows as after the other kernels, and the Lanczos
 // vectors are stored back when the launch ends.  Constant kappa only.
 #include "spde_common.inc"
+#include "spde_coarse8.inc"
 #include "spde_scalar.inc"
 
 namespace spde {
@@ -38,15 +39,14 @@ struct SmallLayout {
   // threads (four by 1024 threads: 24.8 us an iteration, with spills)
   static constexpr int C = LN == 4 ? 8 : 4;
   static constexpr int n = 1 << LN, N = 1 << (3 * LN), T = N / C;
-  // planes of the shared array and of the 8^3 level end in a zero, which the
-  // neighbours outside the box read; the 8^3 level has zero planes at both ends
-  static constexpr int PP = n * n + 1, P8 = 65;
+  // planes of the shared array end in a zero, which the neighbours outside the
+  // box read
+  static constexpr int PP = n * n + 1;
   static constexpr size_t faces = 3 * (size_t)N * sizeof(double);
   static constexpr size_t shared = (size_t)PP * n * sizeof(TM);
-  static constexpr size_t level8 = LN == 4 ? 2 * 10 * P8 * sizeof(TM) : 0;   // x, y of the 8^3 level
-  static constexpr size_t level4 = 2 * 64 * sizeof(TM);
+  static constexpr size_t coarse = (LN == 4 ? Coarse8<TM, false>::words() : 128) * sizeof(TM);
   static constexpr size_t bytes =
-      faces + (2 * (T / 64) + 2) * sizeof(double) + sizeof(Scalars) + shared + level8 + level4;
+      faces + (2 * (T / 64) + 2) * sizeof(double) + sizeof(Scalars) + shared + coarse;
 };
 
 // Threads own columns of C cells along z (cells (i, j, C q .. C q + C - 1)), so
@@ -55,17 +55,14 @@ struct SmallLayout {
 template <typename TM, int LN, int POLY>
 __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx, SmallLevels P, int iters) {
   using S = SmallLayout<TM, LN>;
-  constexpr int n = S::n, N = S::N, T = S::T, PL = n * n, PP = S::PP, P8 = S::P8, C = S::C, Q = n / C;
+  constexpr int n = S::n, N = S::N, T = S::T, PL = n * n, PP = S::PP, C = S::C, Q = n / C;
   extern __shared__ __align__(16) unsigned char smem[];
   double* fs = reinterpret_cast<double*>(smem);                        // [3][N] faces of v_j
   double* red = fs + 3 * N;                                            // [T / 64][2]
   int* go = reinterpret_cast<int*>(red + 2 * (T / 64));                // whether the sample goes on
   Scalars* ss = reinterpret_cast<Scalars*>(red + 2 * (T / 64) + 2);    // the slot's scalars
   TM* sh = reinterpret_cast<TM*>(ss + 1);                              // [n][PP] shared by the stages
-  TM* x8 = sh + PP * n;                                                // [10][P8] 8^3 level (LN = 4)
-  TM* y8 = x8 + (LN == 4 ? 10 * P8 : 0);
-  TM* b4 = y8 + (LN == 4 ? 10 * P8 : 0);                               // 4^3 level
-  TM* x4 = b4 + 64;
+  TM* mem = sh + PP * n;                                               // the coarser levels
   const int slot = blockIdx.x;
   Scalars* SC = F.sc + slot;
   if (SC->state != ST_ACTIVE) return;
@@ -79,8 +76,8 @@ __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx,
   double zs_prev = SC->zs;                                             // 1 / gamma_{j-1}
   if (tid == 0) *ss = *SC;
   if (tid < n) sh[tid * PP + PL] = (TM)0;
-  if constexpr (LN == 4)
-    for (int e = tid; e < 20 * P8; e += T) x8[e] = (TM)0;
+  TM *b4 = mem, *x4 = mem + 64;                                        // 8^3: the 4^3 level
+  Coarse8<TM, false, LN == 4> K8(P.lv[1], P.cinv, mem, tid);                    // 16^3: the 8^3 and 4^3 levels
 
   // ---- constants of the thread's cells
   const Diag<TM> D(P.lv[0].k2, P.lv[0].a);
@@ -106,20 +103,6 @@ __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx,
   auto share = [&](const TM (&v)[C]) {
 #pragma unroll
     for (int r = 0; r < C; ++r) sh[s0 + r * PP] = v[r];
-  };
-  // 8^3 level: one cell per thread, the eight children of a 4^3 cell in
-  // neighbouring lanes
-  const int C4 = tid >> 3, ch = tid & 7;
-  const int i8 = 2 * (C4 & 3) + (ch & 1), j8 = 2 * ((C4 >> 2) & 3) + ((ch >> 1) & 1), l8 = 2 * (C4 >> 4) + (ch >> 2);
-  int s8 = i8 + 8 * j8 + P8 * (l8 + 1), z8 = 64 + P8 * (l8 + 1);
-  const TM a8 = LN == 4 ? (TM)P.lv[1].a : (TM)0, k28 = LN == 4 ? (TM)P.lv[1].k2 : (TM)0;
-  const TM e0 = LN == 4 ? (TM)P.lv[1].c0 : (TM)0, e1 = LN == 4 ? (TM)P.lv[1].c1 : (TM)0,
-           e2 = LN == 4 ? (TM)P.lv[1].c2 : (TM)0;
-  auto nn8 = [](int x, int y, int z) { return (x > 0) + (x < 7) + (y > 0) + (y < 7) + (z > 0) + (z < 7); };
-  const TM d8 = k28 + a8 * (TM)nn8(i8, j8, l8), v8 = (TM)1 / (LN == 4 ? d8 : (TM)1);
-  auto sum8 = [&](const TM* v) {
-    return v[i8 > 0 ? s8 - 1 : z8] + v[i8 < 7 ? s8 + 1 : z8] + v[j8 > 0 ? s8 - 8 : z8] + v[j8 < 7 ? s8 + 8 : z8] +
-           v[s8 - P8] + v[s8 + P8];
   };
   // exact 4^3 solve: T / 64 lanes per row, each with 64 * 64 / T products
   constexpr int RL = T / 64, RP = 64 / RL;
@@ -167,7 +150,7 @@ __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx,
     // iteration needs
     asm volatile("" : "+v"(ox), "+v"(oy), "+v"(neg), "+v"(dI), "+v"(dB), "+v"(vI), "+v"(vB));
     asm volatile("" : "+v"(c0), "+v"(s0), "+v"(nxm), "+v"(nxp), "+v"(nym), "+v"(nyp), "+v"(rowx), "+v"(rowy),
-                 "+v"(s8), "+v"(z8), "+v"(pz));
+                 "+v"(K8.at), "+v"(K8.zero), "+v"(pz));
     // pre-smoothing from zero: x = cA bhat + (cB / d) sum bhat
     TM bh[C], xs[C], t[C], w[C];
 #pragma unroll
@@ -196,35 +179,14 @@ __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx,
       v += __shfl_xor(v, n, 64);
       if (!(i & 1) && !(j & 1)) {
         const int I = i >> 1, J = j >> 1, K = C / 2 * q + u;
-        if constexpr (LN == 4) y8[I + 8 * J + P8 * (K + 1)] = v;   // b of the 8^3 level
+        if constexpr (LN == 4) K8.y8[K8.place(I, J, K)] = v;
         else b4[I + 4 * (J + 4 * K)] = v;
       }
     }
     __syncthreads();
-    TM bb = 0, xx = 0, rr = 0;
     if constexpr (LN == 4) {
-      // the 8^3 level from its residual (in y8) to its correction (in x8)
-      {
-        bb = y8[s8];
-        x8[s8] = (e0 * bb) * v8;                                   // y = c0 D^-1 b
-      }
-      __syncthreads();
-      {
-        const TM y = x8[s8];
-        xx = e1 * y + e2 * v8 * (bb - (d8 * y - a8 * sum8(x8)));
-        y8[s8] = xx;
-      }
-      __syncthreads();
-      {
-        TM v = bb - (d8 * xx - a8 * sum8(y8));
-        v += __shfl_xor(v, 1, 64);
-        v += __shfl_xor(v, 2, 64);
-        v += __shfl_xor(v, 4, 64);
-        if (ch == 0) b4[C4] = v;
-      }
-      __syncthreads();
-    }
-    {   // exact solve on the 4^3 level
+      K8.solve(sinv);
+    } else {   // exact solve on the 4^3 level
       const int part = tid & (RL - 1), row = tid / RL;
       TM v = sinv[0] * b4[RP * part];
 #pragma unroll
@@ -232,30 +194,13 @@ __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx,
 #pragma unroll
       for (int o = 1; o < RL; o <<= 1) v += __shfl_xor(v, o, 64);
       if (part == 0) x4[row] = v;
-    }
-    __syncthreads();
-    if constexpr (LN == 4) {
-      {   // x' = x + P x4
-        xx += x4[C4];
-        x8[s8] = xx;
-      }
-      __syncthreads();
-      {   // r = b - A x', y = c0 D^-1 r
-        rr = bb - (d8 * xx - a8 * sum8(x8));
-        y8[s8] = (e0 * rr) * v8;
-      }
-      __syncthreads();
-      {
-        const TM y = y8[s8];
-        x8[s8] = xx + (e1 * y + e2 * v8 * (rr - (d8 * y - a8 * sum8(y8))));
-      }
       __syncthreads();
     }
     // x' = x + P e; r = d (bhat - x') + a sum x'; y = c0 D^-1 r
 #pragma unroll
     for (int u = 0; u < C / 2; ++u) {
       const int I = i >> 1, J = j >> 1, K = C / 2 * q + u;
-      const TM e = LN == 4 ? x8[I + 8 * J + P8 * (K + 1)] : x4[I + 4 * (J + 4 * K)];
+      const TM e = LN == 4 ? K8.x8[K8.place(I, J, K)] : x4[I + 4 * (J + 4 * K)];
       xs[2 * u] += e;
       xs[2 * u + 1] += e;
     }
