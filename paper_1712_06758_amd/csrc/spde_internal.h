@@ -251,6 +251,8 @@ hipError_t launch_transfer_fill(int n, const double* xyz, int64_t n_vert, const 
 hipError_t launch_set_state(Scalars* sc, int slot0, int count, int state, hipStream_t st);
 // Per-sample scalars of a steady-state operator pass (autotuner timing).
 hipError_t launch_tune_scalars(Scalars* sc, int batch, hipStream_t st);
+// One wave that sleeps for some 80 us.
+hipError_t launch_hold(hipStream_t st);
 hipError_t launch_mg_down(bool fp64, int shape, bool fine, const void* b0, const void* b1, void* rH,
                           const Level& L, int batch, const Scalars* sc, hipStream_t st);
 // The finest level's output of a slot in iteration j goes to o + (j & om) ostr

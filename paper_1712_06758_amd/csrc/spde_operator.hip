@@ -21,8 +21,8 @@ __device__ __forceinline__ void operator_block(const Fields& F, int nb, int& slo
     slot_block(blockIdx.x, gridDim.x, nb, slot, blk);
   } else {
     const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    slot = lb / nb;
-    blk = lb - slot * nb;
+    slot = lb >> ilog2(nb);
+    blk = lb & (nb - 1);
   }
 }
 
@@ -114,8 +114,8 @@ __global__ __launch_bounds__(kBlock) void k_operator_col(Fields F, Box bx, int n
   const int64_t nc = bx.nc;
   const int n = bx.n;
   const int64_t n2 = bx.n2;
-  const int tpx = n >> 6, tpy = n >> 2;
-  const int x0 = (t % tpx) << 6, y0 = ((t / tpx) % tpy) << 2, z0 = (t / (tpx * tpy)) * ZC;
+  int x0, y0, z0;
+  tile_origin<64, 4, ZC>(t, n, x0, y0, z0);
   const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int i = x0 + lane;
   const int jj = __builtin_amdgcn_readfirstlane(y0 + wv);

@@ -56,3 +56,35 @@ def test_vcycle_matches_numpy(n, batch, precision, bar):
     z = box.apply_vcycle(torch.tensor(r, device="cuda")).cpu().numpy()
     ref = vcycle(kappa, r.reshape(batch, n, n, n)).reshape(batch, -1)
     assert max(rel_l2(z[b], ref[b]) for b in range(batch)) <= bar
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("precision,shapes", [("fp64", (1, 4, 5)), ("mixed", (0, 1, 2, 3, 4, 5))])
+def test_samples_with_3d_tiles(precision, shapes, kind):
+    """The partial sums of the finest up kernel: every 3-D tile shape reaches the
+    oracle, with constant kappa and with a cell-wise one (constant multigrid)."""
+    from tests.gpu_common import gval, oracle_u
+    torch = pytest.importorskip("torch")
+    import paper_1712_06758_amd as P
+    n, kappa, batch = 32, 12.0, 3
+    bar = {"fp64": 1e-10, "mixed": 1e-7}[precision]
+    rng = np.random.default_rng(31 + kind)
+    xi = rng.standard_normal((batch, n ** 3))
+    xd = torch.tensor(xi, device="cuda")
+    ref = oracle_u(n, kappa, gval(kappa), xi)
+    kc = kappa * (1.0 + 0.2 * rng.random(n ** 3))
+    box = P.Box(n, kappa, precision=precision, max_batch=batch)
+    box.set_face_preconditioner(kind)
+    var = P.Box(n, kappa, precision=precision, max_batch=batch)
+    var.set_face_preconditioner(kind)
+    var.set_coefficients(kc, None, kappa_ref=kappa)
+    var.set_tiles(10, 10)
+    want = var.sample(xd, u_box=True)["u_box"].cpu().numpy()
+    for shape in shapes:
+        say(f"3-D tile {shape} {precision} face block {kind}")
+        box.set_tiles(shape, shape)
+        u = box.sample(xd, u_box=True)["u_box"].cpu().numpy()
+        assert max(rel_l2(u[b], ref[b]) for b in range(batch)) <= bar
+        var.set_tiles(shape, shape)
+        u = var.sample(xd, u_box=True)["u_box"].cpu().numpy()
+        assert max(rel_l2(u[b], want[b]) for b in range(batch)) <= 2 * bar
