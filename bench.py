@@ -28,7 +28,8 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBS = 8000.0
 # the kernel sources and build flags that the counter traffic in profiles/ was taken with
 HASHED_SOURCES = ("spde_kernels.hip", "spde_operator.hip", "spde_mg_f32.hip", "spde_mg_f64.hip", "spde_common.inc",
-                  "spde_mg.inc", "spde_mg_launch.inc", "spde_vcycle.inc", "spde_launch.inc", "spde_internal.h")
+                  "spde_mg.inc", "spde_mg_launch.inc", "spde_vcycle.inc", "spde_coarse8.inc", "spde_scalar.inc",
+                  "spde_launch.inc", "spde_internal.h")
 
 
 def log(msg):

@@ -11,7 +11,7 @@
 // Per iteration j (all launches cover every slot of the batch; each block
 // reads its slot's state and exits unless the slot is iterating):
 //   mg_down (fine, then per level)  : smooth from zero, restrict the residual
-//   mg_coarse                        : the levels that fit in LDS, one block per slot
+//   mg_coarse                        : the levels from 16^3 down, one block per slot
 //   mg_up (per level, then fine)     : prolong, correct, smooth; the fine launch
 //                                      writes zhat_j and the partial sums of
 //                                      <zhat_j, v_j> and zhat_j^T A zhat_j
@@ -20,6 +20,8 @@
 //   operator                         : v_{j+1} = A z_j - (delta/gamma) v_j - (gamma/gamma_prev) v_{j-1}
 // and every few iterations
 //   direction                        : the direction and solution updates of those iterations
+// Boxes of 8^3 and 16^3 with constant kappa run all of it but the direction pass
+// in one launch (spde_small.hip).
 #include <mutex>
 
 #include "spde_common.inc"
