@@ -842,6 +842,7 @@ spde_status spde_configure(spde_handle h, spde_precision prec, double rtol, int 
   c->max_batch = max_batch;
   c->configured = true;
   c->box.poly = c->face_precond;
+  c->expect_iters = 0;   // another tolerance, precision or cap
   c->ws = nullptr;
   c->ws_bytes = 0;
   c->tuned = false;
@@ -1196,6 +1197,9 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
   auto iterate = [&](int expect, int& launched) -> spde_status {
     launched = 0;
     const int cap = c->max_iter + 2;
+    // below cap, so that the loop never ends on a block without a poll: what the
+    // call returns is read from the states that its own last poll copied
+    expect = std::min(expect, c->max_iter + 1);
     bool all_done = false;
     while (!all_done && launched < cap + c->poll) {
       int count = c->poll;
