@@ -361,7 +361,9 @@ spde_status spde_slots_poll(spde_handle h, int nslots, int* state_host, int* ite
                             void* stream);
 
 /* Write the field of a converged slot to u_box_dev [n^3] (nullable: discard)
- * and mark the slot idle.  Asynchronous on `stream`. */
+ * and mark the slot idle.  Asynchronous on `stream`.  The field is final once
+ * the step in which the slot converged has ended on the device: it may then be
+ * written on another stream while the other slots go on. */
 spde_status spde_slot_finish(spde_handle h, int slot, double* u_box_dev, void* stream);
 
 /* Stateless CSR SpMM y[b] = A x[b] for b < batch (the transfer apply with an

@@ -110,7 +110,7 @@ struct Ctx {
   bool mg_dirty = false;        // the level diagonals must be rebuilt before the next solve
   double* resid_out = nullptr;  // [max_batch]
   int ring = kRing;             // entries of the zhat ring (kRing or 2)
-  int unapplied = 0;            // iterations enqueued since the last direction pass (at most ring)
+  int unapplied = 0;            // updates that an iterating slot may have waiting after a step (at most ring)
   int slots_hi = 0;             // slots [0, slots_hi) have been initialised since the workspace was bound
   hipStream_t own_stream = nullptr;
   hipStream_t aux_stream = nullptr;   // second half of a split batch
@@ -396,19 +396,21 @@ spde_status enqueue_operator(Ctx* c, const View& V, int batch, hipStream_t st, i
   return SPDE_OK;
 }
 
-// Direction pass over the slots of V (`count` iterations up to `iter` are waiting).
-spde_status enqueue_direction(Ctx* c, const View& V, int batch, hipStream_t st, int iter, int count) {
+// Direction pass over the slots of V (`count` iterations up to `iter` are
+// waiting): every slot's, or the finished slots' only.
+spde_status enqueue_direction(Ctx* c, const View& V, int batch, hipStream_t st, int iter, int count,
+                              bool finished_only = false) {
   Timed t(c, KID_DIRECTION, iter, st, count, V.s0, batch);
-  HIPCHK(launch_direction(c->fp64(), V.F, c->box, batch, st));
+  HIPCHK(launch_direction(c->fp64(), V.F, c->box, batch, finished_only, st));
   return SPDE_OK;
 }
 
-// Apply every slot's waiting direction and solution updates.
-spde_status apply_waiting(Ctx* c, hipStream_t st, int iter) {
-  if (!c->unapplied || !c->slots_hi) return SPDE_OK;
-  spde_status s = enqueue_direction(c, make_view(c, 0), c->slots_hi, st, iter, c->unapplied);
-  if (s == SPDE_OK) c->unapplied = 0;
-  return s;
+// Whether a caller is capturing the stream: what is enqueued then runs any number
+// of times, later, and moves none of the handle's host-side counts.
+bool being_captured(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) { hipGetLastError(); return false; }
+  return cap == hipStreamCaptureStatusActive;
 }
 
 spde_status enqueue_iteration(Ctx* c, const View& V, int batch, hipStream_t st, int iter) {
@@ -1117,9 +1119,6 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
   if (s != SPDE_OK) return s;
   s = prepare_mg_coeffs(c, st);
   if (s != SPDE_OK) return s;
-  // updates that other slots of the handle still wait for
-  s = apply_waiting(c, st, 0);
-  if (s != SPDE_OK) return s;
   c->slots_hi = std::max(c->slots_hi, batch);
   // the load F_u: the caller's noise, or the generated noise drawn again into
   // a Lanczos buffer that no running solve uses
@@ -1201,11 +1200,11 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
     // call returns is read from the states that its own last poll copied
     expect = std::min(expect, c->max_iter + 1);
     bool all_done = false;
+    int waiting = 0;   // updates in the ring (the same for both halves)
     while (!all_done && launched < cap + c->poll) {
       int count = c->poll;
       // (the small boxes, whose launches take whole iterations, as one block)
       if (expect > launched) count = small ? expect - launched : std::min(count, expect - launched);
-      int waiting = c->unapplied;   // the same for both halves
       if (split) {
         int w1 = waiting;
         spde_status s2 = enqueue_block(c, V1, batch - b1, c->aux_stream, graphs, launched, count, &w1);
@@ -1213,7 +1212,6 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
       }
       spde_status s2 = enqueue_block(c, V0, b1, st, graphs, launched, count, &waiting);
       if (s2 != SPDE_OK) return s2;
-      c->unapplied = waiting;
       if (split) {
         HIPCHK(hipEventRecord(c->ev_join, c->aux_stream));
         HIPCHK(hipStreamWaitEvent(st, c->ev_join, 0));
@@ -1227,7 +1225,7 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
         if (c->host_sc[b].state == ST_ACTIVE) { all_done = false; break; }
       }
     }
-    return apply_waiting(c, st, launched);
+    return waiting ? enqueue_direction(c, V0, batch, st, launched, waiting) : SPDE_OK;
   };
   int launched = 0;
   s = iterate(c->expect_iters, launched);
@@ -1466,17 +1464,16 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
   // A caller may be capturing the stream and replay these launches any number
   // of times: the direction passes are then part of what is captured, with
   // nothing left waiting before or after.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess) { hipGetLastError(); cap = hipStreamCaptureStatusNone; }
-  const bool captured = cap == hipStreamCaptureStatusActive;
+  const bool captured = being_captured(st);
   c->slots_hi = std::max(c->slots_hi, nslots);
   if (captured) {
     s = enqueue_direction(c, V0, c->slots_hi, st, 0, c->ring);
     if (s != SPDE_OK) return s;
   }
+  const int most = std::min({iters, c->poll, c->ring});   // iterations of a chunk
   int waiting = captured ? 0 : c->unapplied;
   for (int done = 0; done < iters;) {
-    const int chunk = std::min({iters - done, c->poll, c->ring});
+    const int chunk = std::min(iters - done, most);
     if (waiting + chunk > c->ring) {
       s = enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
       if (s != SPDE_OK) return s;
@@ -1488,8 +1485,14 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
     if (!captured) c->unapplied = waiting;
     done += chunk;
   }
-  if (captured) return enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
-  return SPDE_OK;
+  // A step leaves the fields of the slots that have finished final, so that no
+  // later call has anything to add to them or can disturb them, on whatever
+  // stream it runs; the others' updates may wait for as long as the ring holds
+  // another step's.
+  if (!captured && waiting + most <= c->ring) return enqueue_direction(c, V0, nslots, st, 0, waiting, true);
+  s = enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
+  if (s == SPDE_OK && !captured) c->unapplied = 0;
+  return s;
 }
 
 spde_status spde_slots_poll(spde_handle h, int nslots, int* state_host, int* iters_host, void* stream) {
@@ -1523,8 +1526,10 @@ spde_status spde_slot_finish(spde_handle h, int slot, double* u_box_dev, void* s
   if (slot < 0 || slot >= c->max_batch) return fail(SPDE_EINVAL, "slot out of range");
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = pick_stream(c, stream);
-  s = apply_waiting(c, st, 0);
-  if (s != SPDE_OK) return s;
+  if (c->unapplied || being_captured(st)) {   // a slot that still iterates; a finished one has nothing waiting
+    s = enqueue_direction(c, make_view(c, slot), 1, st, 0, c->ring);
+    if (s != SPDE_OK) return s;
+  }
   HIPCHK(launch_fix_solution(c->F, c->box, 1, slot, st));
   if (u_box_dev)
     HIPCHK(hipMemcpyAsync(u_box_dev, c->F.x + cell_off(slot, c->box.nc), c->box.nc * 8, hipMemcpyDeviceToDevice,

@@ -287,9 +287,10 @@ hipError_t launch_operator(bool z_fp64, const Fields& F, const Box& bx, int batc
 bool small_box(const Box& bx, const Level& top);
 hipError_t launch_small(bool fp64, const Fields& F, const Box& bx, const Level& top, const Level& next,
                         const void* cinv, int batch, int iters, hipStream_t st);
-// Apply the waiting direction and solution updates of the slots (a slot with
-// none is left as it is).
-hipError_t launch_direction(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st);
+// Apply the waiting direction and solution updates of the slots, or of the
+// finished ones only (a slot with none is left as it is).
+hipError_t launch_direction(bool z_fp64, const Fields& F, const Box& bx, int batch, bool finished_only,
+                            hipStream_t st);
 hipError_t launch_fix_solution(const Fields& F, const Box& bx, int batch, int slot0, hipStream_t st);
 hipError_t launch_flux(const double* u, double* sig_int, double* sig_ext, const Box& bx, int batch,
                        hipStream_t st);
