@@ -1638,6 +1638,12 @@ spde_status spde_apply_vcycle(spde_handle h, int batch, const double* r_dev, dou
   if (s != SPDE_OK) return s;
   s = prepare_mg_coeffs(c, st);
   if (s != SPDE_OK) return s;
+  // float32 levels write into the ring, where updates of slots that iterate may
+  // wait: these are applied first (a replay may find some where now there are none)
+  if (!c->fp64() && (c->unapplied || being_captured(st))) {
+    s = enqueue_direction(c, make_view(c, 0), batch, st, 0, c->ring);
+    if (s != SPDE_OK) return s;
+  }
   // the finest up kernel always writes partial sums: give it the solver's buffer
   s = enqueue_vcycle(c, make_view(c, 0), batch, st, 0, r_dev, r_dev, out, 0, 0, nullptr, c->F.part_up);
   if (s != SPDE_OK) return s;

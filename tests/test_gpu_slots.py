@@ -180,3 +180,40 @@ def test_fetch_on_a_second_stream(n, precision):
         u = out[s] if s in out else S.finish(s)
         S.st.synchronize()
         assert torch.equal(u, want[s]), s
+
+
+@pytest.mark.parametrize("n,precision", [(16, "mixed"), (32, "mixed"), (64, "mixed"), (32, "fp64")])
+@pytest.mark.parametrize("iters", [3, 12, 16])
+def test_vcycle_leaves_running_slots(n, precision, iters):
+    """The V-cycle check between the steps of running slots, called and replayed."""
+    torch, P, _ = _setup()
+    say(f"V-cycle beside running slots n={n} {precision} after {iters}")
+    S = Slots(n, precision, 2)
+    S.run(4, want=2)
+    want = [S.finish(s) for s in range(2)]
+    r = torch.randn(2, n ** 3, generator=torch.Generator(device="cuda").manual_seed(9), device="cuda",
+                    dtype=torch.float64)
+    z0 = S.box.apply_vcycle(r)
+    S.st.synchronize()
+    z = torch.empty_like(r)
+    g = torch.cuda.CUDAGraph()               # captured while nothing waits
+    with torch.cuda.graph(g, stream=S.st):
+        S.check(S.L.spde_apply_vcycle(S.h, 2, C.c_void_p(r.data_ptr()), C.c_void_p(z.data_ptr()), S.sp))
+    for how in ("called", "replayed"):
+        S.start(range(2))
+        S.step(iters)
+        S.st.synchronize()
+        if how == "called":
+            z.copy_(S.box.apply_vcycle(r))
+        else:
+            z.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(S.st):
+                g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(z, z0)
+        S.run(4, want=2)
+        got = [S.finish(s) for s in range(2)]
+        S.st.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), how
