@@ -134,7 +134,9 @@ struct Ctx {
   int poll = 8;
   std::map<int64_t, hipGraphExec_t> graphs;   // (first slot, half-iterations, batch) -> graph
   int split = 1;                 // 2: batches of 8+ run as two halves on two streams
-  int expect_iters = 0;          // iterations (incl. the one that finds convergence) the last call needed
+  // iterations (incl. the one that finds convergence) that the last cold and the last
+  // warm-started call of this configuration and these coefficients needed (0: unknown)
+  int expect_iters[2] = {0, 0};
   double refine_target = 0.0;     // > 0: refine until ||F - A U|| / ||F|| <= target (float64 residuals)
   int refine_max = 0;             // at most this many refinement passes
   bool tuned = false;
@@ -159,6 +161,9 @@ struct Ctx {
 }  // namespace spde
 
 namespace {
+
+// What the calls so far needed says nothing about the next one.
+void forget_iters(Ctx* c) { c->expect_iters[0] = c->expect_iters[1] = 0; }
 
 // Chebyshev degree-2 smoother coefficients on [lmax/4, lmax] of D^-1 S~, with
 // lmax the Gershgorin bound (k2 + 12 a) / (k2 + 6 a) (capped at 2).
@@ -844,7 +849,7 @@ spde_status spde_configure(spde_handle h, spde_precision prec, double rtol, int 
   c->max_batch = max_batch;
   c->configured = true;
   c->box.poly = c->face_precond;
-  c->expect_iters = 0;   // another tolerance, precision or cap
+  forget_iters(c);   // another tolerance, precision or cap
   c->ws = nullptr;
   c->ws_bytes = 0;
   c->tuned = false;
@@ -858,6 +863,7 @@ spde_status spde_set_coefficients(spde_handle h, const double* kappa_dev, const 
   if (kappa_ref != 0.0 && !(kappa_ref > 0.0 && std::isfinite(kappa_ref)))
     return fail(SPDE_EINVAL, "kappa_ref must be 0 or positive and finite");
   drop_graphs(c);   // kernel arguments change
+  forget_iters(c);
   c->box.kap = kappa_dev;
   c->box.gfld = g_dev;
   // kappa field with kappa_ref = 0: the multigrid takes the cell-wise kappa
@@ -1186,12 +1192,12 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
     HIPCHK(hipStreamWaitEvent(c->aux_stream, c->ev_fork, 0));
   }
   // MINRES iterations in blocks of the poll interval until no sample is active.
-  // expect: iterations the previous call needed (0: unknown); the blocks up to
-  // it are enqueued without a poll, and the block that would pass it stops
-  // there, so that a batch like the last one is neither held up by polls nor
+  // expect: iterations the previous call of the kind needed (0: unknown); the
+  // blocks up to it are enqueued without a poll, and the block that would pass it
+  // stops there, so that a batch like the last one is neither held up by polls nor
   // carried through idle iterations (a batch that needs fewer finds its samples
-  // done, and every kernel leaves at once).  Polls held up a 16^3 call, whose
-  // iterations take 33 us, by 70 us in all.
+  // done, and every kernel leaves at once).  A poll holds up a small box by 10 us
+  // (64^3 x 1: 70 us a call in all).
   const bool small = small_box(bx, c->lv[0]);
   auto iterate = [&](int expect, int& launched) -> spde_status {
     launched = 0;
@@ -1228,7 +1234,8 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
     return waiting ? enqueue_direction(c, V0, batch, st, launched, waiting) : SPDE_OK;
   };
   int launched = 0;
-  s = iterate(c->expect_iters, launched);
+  int& expect = c->expect_iters[warm_uc ? 1 : 0];
+  s = iterate(expect, launched);
   if (s != SPDE_OK) return s;
   bool notconv = false, failed = false;
   int most = 0;
@@ -1242,7 +1249,7 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
     if (sc.state == ST_DONE) most = std::max(most, sc.iters);
   }
   // a converged sample needs its iterations and the V-part that finds it converged
-  c->expect_iters = (!notconv && !failed && most > 0) ? most + 1 : 0;
+  expect = (!notconv && !failed && most > 0) ? most + 1 : 0;
   HIPCHK(launch_fix_solution(c->F, bx, batch, 0, st));
   // Iterative refinement in float64: with r = F - A U (flux recovered from U,
   // so only the cell row is nonzero), solve A d = r by the same MINRES and set
@@ -1856,6 +1863,7 @@ spde_status spde_set_face_preconditioner(spde_handle h, int kind) {
   Ctx* c = reinterpret_cast<Ctx*>(h);
   if (!c) return fail(SPDE_EINVAL, "null handle");
   if (kind != 0 && kind != 1) return fail(SPDE_EINVAL, "face preconditioner must be 0 or 1");
+  if (kind != c->face_precond) forget_iters(c);
   c->face_precond = kind;
   c->box.poly = kind;
   drop_graphs(c);

@@ -65,3 +65,51 @@ def test_a_breakdown_is_reported_after_reconfiguring():
     out = box.sample(xi, u_box=True, allow_notconv=True, allow_failed=True)
     assert out["status"] == P.SPDE_EFAILED
     assert torch.isnan(out["u_box"][1]).all() and not torch.isnan(out["u_box"][0]).any()
+
+
+def _launched(box, call):
+    """The call's result and the iterations that it enqueued (operator launches)."""
+    box.timing(-1)
+    box.timing(1)
+    try:
+        out = call()
+        return out, box.timing_report()["operator"]["launches"]
+    finally:
+        box.timing(0)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("change", ["coefficients", "face", "warm"])
+def test_no_iterations_beyond_a_poll(precision, change):
+    """A call that needs fewer iterations than the one before, because the coefficients,
+    the face block or the kind of start changed, stops at the next poll."""
+    torch, P = _setup()
+    n, poll = 32, 8
+    say(f"idle iterations after a change of {change}, {precision}")
+    g = torch.Generator(device="cuda").manual_seed(4)
+    xi = torch.randn(2, n ** 3, generator=g, device="cuda", dtype=torch.float64)
+    box = P.Box(n, 10.0, precision=precision, max_batch=2)
+    box.set_poll_interval(poll)
+    if change == "coefficients":
+        rough = 10.0 * torch.exp(0.6 * torch.randn(n ** 3, generator=g, device="cuda", dtype=torch.float64))
+        box.set_coefficients(kappa=rough, kappa_ref=10.0)
+        before = box.sample(xi, u_box=True)["iters"]
+        box.set_coefficients()
+        out, count = _launched(box, lambda: box.sample(xi, u_box=True))
+    elif change == "face":
+        box.set_face_preconditioner(0)
+        before = box.sample(xi, u_box=True)["iters"]
+        box.set_face_preconditioner(1)
+        out, count = _launched(box, lambda: box.sample(xi, u_box=True))
+    else:
+        # a load that the coarse grid holds exactly: the warm start has next to nothing left to do
+        before = box.sample(xi, u_box=True)["iters"]
+        flat = torch.ones(2, n ** 3, device="cuda", dtype=torch.float64)
+        u = box.sample(flat, u_box=True)["u_box"]
+        box.sample(xi, u_box=True)
+        uc = u[:, : (n // 2) ** 3].contiguous()
+        out, count = _launched(box, lambda: box.sample_warm(flat, uc, u_box=True))
+    say(f"  iterations {before} before, {out['iters']} now, {count} enqueued")
+    most = -(-(int(out["iters"].max()) + 1) // poll) * poll
+    assert before.max() >= most
+    assert count <= most
