@@ -88,13 +88,19 @@ spde_status spde_setup_box(int n, double kappa, double g, spde_handle* out);
 spde_status spde_configure(spde_handle h, spde_precision prec, double rtol,
                            int max_iter, int max_batch);
 
-/* Device workspace size in bytes needed by the current configuration.  On a
- * handle with a bound workspace the query leaves that binding in use. */
+/* Device workspace size in bytes for the current configuration: the size it runs
+ * fastest with, and the least it runs in (about 219 and 107 bytes per cell and
+ * sample in float64, 153 and 97 in mixed precision).  What lies between deepens the
+ * ring in which solution updates wait to be applied together, from 2 iterations to
+ * 4, 8 or 16; results do not depend on it.  On a handle with a bound workspace the
+ * queries leave that binding in use. */
 size_t spde_workspace_bytes(spde_handle h);
+size_t spde_workspace_bytes_min(spde_handle h);
 
-/* Bind a caller-owned device buffer of at least spde_workspace_bytes() bytes,
- * 256-byte aligned.  The buffer must outlive every call that uses the handle.
- * Selects the current HIP device as the handle's device. */
+/* Bind a caller-owned device buffer of at least spde_workspace_bytes_min() bytes,
+ * 256-byte aligned; the deepest ring that it holds is used.  The buffer must
+ * outlive every call that uses the handle.  Selects the current HIP device as the
+ * handle's device. */
 spde_status spde_bind_workspace(spde_handle h, void* dev_ptr, size_t bytes);
 
 /* ---- L2 projection onto a tetrahedral mesh (Sec. "L2-Projection") ------- */

@@ -280,7 +280,11 @@ class Box:
         _abi.check(L.spde_configure(self._hh.h, prec, self.rtol, int(max_iter), self.max_batch))
         nbytes = L.spde_workspace_bytes(self._hh.h)
         with torch.cuda.device(self.device):
-            self._ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            try:
+                self._ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            except torch.OutOfMemoryError:   # the least it runs in, where that is still free
+                nbytes = L.spde_workspace_bytes_min(self._hh.h)
+                self._ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
             _abi.check(L.spde_bind_workspace(self._hh.h, _ptr(self._ws), nbytes))
         self.n_tet = 0
         self._pi = None

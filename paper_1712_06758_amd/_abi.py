@@ -26,6 +26,7 @@ SIGNATURES = {
     "spde_setup_box": (C.c_int, [C.c_int, C.c_double, C.c_double, C.POINTER(_vp)]),
     "spde_configure": (C.c_int, [_vp, C.c_int, C.c_double, C.c_int, C.c_int]),
     "spde_workspace_bytes": (C.c_size_t, [_vp]),
+    "spde_workspace_bytes_min": (C.c_size_t, [_vp]),
     "spde_bind_workspace": (C.c_int, [_vp, _vp, C.c_size_t]),
     "spde_build_transfer": (C.c_int, [_vp, C.c_int64, _vp, C.c_int64, _vp, C.POINTER(_i64p),
                                       C.POINTER(C.POINTER(C.c_int32)), C.POINTER(C.POINTER(C.c_double)),

@@ -109,7 +109,7 @@ struct Ctx {
   bool mg_cellwise = false;     // the kappa field enters the multigrid (Galerkin coarse kappa^2)
   bool mg_dirty = false;        // the level diagonals must be rebuilt before the next solve
   double* resid_out = nullptr;  // [max_batch]
-  int ring = kRing;             // entries of the zhat ring (kRing or 2)
+  int ring = kRing;             // entries of the zhat ring (kRing, or fewer in a smaller workspace)
   int unapplied = 0;            // updates that an iterating slot may have waiting after a step (at most ring)
   int slots_hi = 0;             // slots [0, slots_hi) have been initialised since the workspace was bound
   hipStream_t own_stream = nullptr;
@@ -211,7 +211,16 @@ void plan_hierarchy(Ctx* c) {
   c->nb_pb = operator_blocks(c->box);
 }
 
-size_t layout(Ctx* c, char* base) {
+// The deepest ring that the recommended workspace holds.
+int ring_wanted(const Ctx* c) {
+  int ring = kRing;
+  while (ring > kRingLeast &&
+         (double)ring * (double)c->max_batch * (double)c->box.nc * (double)c->szm() > kRingBytes)
+    ring /= 2;
+  return ring;
+}
+
+size_t layout(Ctx* c, char* base, int ring) {
   const int64_t nc = c->box.nc;
   const size_t B = (size_t)c->max_batch;
   size_t off = 0;
@@ -222,7 +231,7 @@ size_t layout(Ctx* c, char* base) {
   };
   for (int p = 0; p < 2; ++p) c->F.vs[p] = (double*)take(B * 3 * nc * 8);
   for (int p = 0; p < 2; ++p) c->F.vu[p] = (double*)take(B * nc * 8);
-  c->ring = (double)B * (double)nc * (double)c->szm() * kRing <= kRingBytes ? kRing : 2;
+  c->ring = ring;
   c->F.z = (void*)take((size_t)c->ring * B * nc * c->szm());
   c->F.zstr = (int64_t)B * nc;
   c->F.zm = c->ring - 1;
@@ -879,10 +888,12 @@ spde_status spde_set_coefficients(spde_handle h, const double* kappa_dev, const 
   return SPDE_OK;
 }
 
-// Bytes the layout needs, leaving the handle's bound pointers as they are
-// (a size-only layout sets every pointer it lays out to null).
-size_t workspace_size(Ctx* c) {
+// Bytes the layout with a ring of `ring` entries needs, leaving the handle's bound
+// pointers and ring as they are (a size-only layout sets every pointer it lays out
+// to null).
+size_t workspace_size(Ctx* c, int ring) {
   const Fields F = c->F;
+  const int bound_ring = c->ring;
   void* mgb[kMaxLevels];
   void* mge[kMaxLevels];
   void* mgd[kMaxLevels];
@@ -894,8 +905,9 @@ size_t workspace_size(Ctx* c) {
   void* cinv = c->cinv;
   const void* cp_cinv = c->cp.cinv;
   double* resid_out = c->resid_out;
-  const size_t need = layout(c, nullptr);
+  const size_t need = layout(c, nullptr, ring);
   c->F = F;
+  c->ring = bound_ring;
   std::copy(mgb, mgb + kMaxLevels, c->mgb);
   std::copy(mge, mge + kMaxLevels, c->mge);
   std::copy(mgd, mgd + kMaxLevels, c->mgd);
@@ -909,7 +921,13 @@ size_t workspace_size(Ctx* c) {
 size_t spde_workspace_bytes(spde_handle h) {
   Ctx* c = reinterpret_cast<Ctx*>(h);
   if (!c || !c->configured) return 0;
-  return workspace_size(c);
+  return workspace_size(c, ring_wanted(c));
+}
+
+size_t spde_workspace_bytes_min(spde_handle h) {
+  Ctx* c = reinterpret_cast<Ctx*>(h);
+  if (!c || !c->configured) return 0;
+  return workspace_size(c, kRingLeast);
 }
 
 spde_status spde_bind_workspace(spde_handle h, void* dev_ptr, size_t bytes) {
@@ -939,9 +957,12 @@ spde_status spde_bind_workspace(spde_handle h, void* dev_ptr, size_t bytes) {
   }
   drop_graphs(c);
   plan_hierarchy(c);
-  const size_t need = workspace_size(c);
+  // the deepest ring that the buffer holds
+  int ring = kRing;
+  while (ring > kRingLeast && bytes < workspace_size(c, ring)) ring /= 2;
+  const size_t need = workspace_size(c, ring);
   if (bytes < need) return fail(SPDE_ENOMEM, "workspace has %zu bytes, %zu needed", bytes, need);
-  layout(c, (char*)dev_ptr);
+  layout(c, (char*)dev_ptr, ring);
   c->unapplied = 0;
   c->slots_hi = 0;
   c->ws = (char*)dev_ptr;

@@ -73,10 +73,13 @@ struct alignas(16) DirCoef {
 // (float64, 64^3 x 32).  At 128^3 x 1 in float64, where the old pass ran out of
 // the last-level cache: 45.5 -> 38.7 + 5.1 us; 8 entries would leave 7.8 us
 // there, since each pass brings W and x back from memory.  The ring costs kRing
-// sizeof(zhat) bytes of memory per cell; where that would pass kRingBytes, two
-// entries are kept instead (the memory of a double buffer).
-constexpr int kRing = 16;
-constexpr double kRingBytes = 32.0 * 1024 * 1024 * 1024;
+// sizeof(zhat) bytes of memory per cell.  A workspace with less has a shorter one,
+// of 8, 4 or 2 entries (two: the memory of a double buffer), and
+// spde_workspace_bytes asks for the deepest that stays within kRingBytes: one
+// entry of a 128^3 x 64 float64 batch is 1 GiB, so that the largest batches that
+// were measured have all 16, and a handle takes at most 14 GiB more than it must.
+constexpr int kRing = 16, kRingLeast = 2;
+constexpr double kRingBytes = 16.0 * 1024 * 1024 * 1024;
 
 // Box constants.
 struct Box {
