@@ -123,7 +123,9 @@ class GpuEngine:
         L = _abi.lib()
         with torch.cuda.device(device), torch.cuda.stream(self.stream):
             _abi.check(L.spde_slots_reset(self.box._hh.h, slots, self._sp()))
-        self.slot_bytes = self.box.info()["workspace_bytes"] // slots
+        # a slot's share of what the workspace cannot do without: the deeper ring
+        # of a roomy workspace is taken once, at the start, and claims nothing more
+        self.slot_bytes = L.spde_workspace_bytes_min(self.box._hh.h) // slots
         self._state = np.zeros(slots, dtype=np.int32)
         self._iters = np.zeros(slots, dtype=np.int32)
         self._event = None

@@ -59,6 +59,18 @@ def test_alone_equals_mix_and_oracle():
             assert np.abs(got - Pc @ u_c).max() <= 1e-9 * np.abs(Pc @ u_c).max()
 
 
+def test_admission_counts_what_a_slot_must_have():
+    """A budget of two requests of 32^3 (110 bytes of solver state a cell in mixed
+    precision, the noise and the field) has two in flight, and refuses none."""
+    from paper_1712_06758_amd.serve import build_gpu_server
+    say("admission by footprint, level 32")
+    each = (110 + 16) * 32 ** 3
+    srv = build_gpu_server((32,), 0.05, "mixed", slots={32: 8}, hbm_budget=2 * each, reserve_cus=0)
+    rep = srv.run([(0.0, 32, i) for i in range(6)], time_limit=60)
+    assert rep["completed"] == 6 and rep["refused"] == 0
+    assert rep["peak_in_flight_bytes"] == 2 * (srv.engines[32].slot_bytes + 16 * 32 ** 3)
+
+
 def test_mixed_precision_serving_with_128_level():
     """Mixed precision (float32 multigrid), levels 64^3 and 128^3: every 128^3
     request carries its coupled 64^3 coarse part.  24 requests arrive together
