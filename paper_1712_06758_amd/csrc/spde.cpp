@@ -112,6 +112,7 @@ struct Ctx {
   int ring = kRing;             // entries of the zhat ring (kRing, or fewer in a smaller workspace)
   int unapplied = 0;            // updates that an iterating slot may have waiting after a step (at most ring)
   int slots_hi = 0;             // slots [0, slots_hi) have been initialised since the workspace was bound
+  std::vector<char> started;    // [max_batch] slots that were started and not yet fetched
   hipStream_t own_stream = nullptr;
   hipStream_t aux_stream = nullptr;   // second half of a split batch
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -965,6 +966,7 @@ spde_status spde_bind_workspace(spde_handle h, void* dev_ptr, size_t bytes) {
   layout(c, (char*)dev_ptr, ring);
   c->unapplied = 0;
   c->slots_hi = 0;
+  c->started.assign(c->max_batch, 0);
   c->ws = (char*)dev_ptr;
   c->ws_bytes = bytes;
   return SPDE_OK;
@@ -1147,6 +1149,7 @@ spde_status sample_impl(Ctx* c, int batch, const NoiseSrc& src, double* u_tet_de
   s = prepare_mg_coeffs(c, st);
   if (s != SPDE_OK) return s;
   c->slots_hi = std::max(c->slots_hi, batch);
+  std::fill(c->started.begin(), c->started.begin() + batch, 0);
   // the load F_u: the caller's noise, or the generated noise drawn again into
   // a Lanczos buffer that no running solve uses
   const double* xi_res = src.xi;
@@ -1444,6 +1447,7 @@ spde_status spde_slots_reset(spde_handle h, int nslots, void* stream) {
   if (s != SPDE_OK) return s;
   HIPCHK(launch_set_state(c->F.sc, 0, nslots, ST_IDLE, st));
   c->slots_hi = std::max(c->slots_hi, nslots);
+  std::fill(c->started.begin(), c->started.begin() + nslots, 0);
   return SPDE_OK;
 }
 
@@ -1458,6 +1462,7 @@ spde_status spde_slot_start(spde_handle h, int slot, const double* xi_dev, void*
   const double scale = -c->g * std::pow(c->box.h, 1.5);
   HIPCHK(launch_init(c->F, c->box, xi_dev, scale, 1, c->rtol, c->max_iter, slot, st));
   c->slots_hi = std::max(c->slots_hi, slot + 1);
+  c->started[slot] = 1;
   return SPDE_OK;
 }
 
@@ -1475,7 +1480,22 @@ spde_status spde_slot_start_seeded(spde_handle h, int slot, uint64_t seed, uint6
   const double scale = -c->g * std::pow(c->box.h, 1.5);
   HIPCHK(launch_init_gen(c->F, c->box, seed, event, coupled, scale, 1, c->rtol, c->max_iter, slot, st));
   c->slots_hi = std::max(c->slots_hi, slot + 1);
+  c->started[slot] = 1;
   return SPDE_OK;
+}
+
+// Whether a step's operator launches deal their slots out to the XCDs in turn
+// (operator_block).  In ranges of slots, one per XCD, a slot's planes stay in one
+// L2, and the column kernel of boxes from 64^3 up gains by it while most slots are
+// busy; with many idle ones their XCDs have nothing to do.  Time of an iteration
+// in ranges against in turn, 16 / 14 / 12 / 8 of 16 slots busy: 128^3 mixed 0.93,
+// 0.95, 0.94, 1.22; 64 slots of 64^3 mixed 0.98, 0.98, 1.07, 1.30; 32 of 64^3
+// float64 0.95, 0.98, 1.00, 1.18.  The kernel of smaller boxes gains nothing: 128
+// of 32^3 mixed 1.03, 1.07, 1.11, 1.27.
+static int spread_slots(const Ctx* c, int nslots) {
+  if (c->n < 64) return 1;
+  const int64_t busy = std::count(c->started.begin(), c->started.begin() + nslots, 1);
+  return 8 * busy < 7 * (int64_t)nslots;
 }
 
 spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) {
@@ -1488,7 +1508,7 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
   hipStream_t st = pick_stream(c, stream);
   const bool graphs = c->use_graphs && c->timing != 1 && st != nullptr;
   View V0 = make_view(c, 0);
-  V0.F.spread = 1;
+  V0.F.spread = spread_slots(c, nslots);
   // A caller may be capturing the stream and replay these launches any number
   // of times: the direction passes are then part of what is captured, with
   // nothing left waiting before or after.
@@ -1563,6 +1583,7 @@ spde_status spde_slot_finish(spde_handle h, int slot, double* u_box_dev, void* s
     HIPCHK(hipMemcpyAsync(u_box_dev, c->F.x + cell_off(slot, c->box.nc), c->box.nc * 8, hipMemcpyDeviceToDevice,
                           st));
   HIPCHK(launch_set_state(c->F.sc, slot, 1, ST_IDLE, st));
+  c->started[slot] = 0;
   return SPDE_OK;
 }
 

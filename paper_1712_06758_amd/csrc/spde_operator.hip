@@ -12,8 +12,8 @@ namespace spde {
 //   (B^T z_u)_face = h^2 (zhat[c - e_d] - zhat[c]) / gamma
 //   (A z)_cell = (h^2 q sum_d (z_hi - z_lo) / q - kappa^2 h^3 zhat) / gamma
 
-// Slot and block of an operator launch.  Slots that all iterate run in
-// contiguous ranges, one range per XCD; a partly filled engine deals its slots
+// Slot and block of an operator launch.  Slots that all or nearly all iterate run
+// in contiguous ranges, one range per XCD; a partly filled engine deals its slots
 // out in turn.  (The turn costs the pass 15 % where every slot is busy: 64^3 x 32
 // float64 148 -> 170 us; the level kernels run the same either way.)
 __device__ __forceinline__ void operator_block(const Fields& F, int nb, int& slot, int& blk) {

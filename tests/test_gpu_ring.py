@@ -124,6 +124,7 @@ def test_slots_keep_their_bits(n, precision, ring):
     xi = P.noise(n, 7, batch=slots)
     box = P.Box(n, 10.0, precision=precision, max_batch=slots)
     base = box.sample(xi, u_box=True)
+    torch.cuda.synchronize()
     _bind(box, abi, ring)
     for lvl, (d, s) in enumerate(base["tiles"]):
         box.set_tiles(d, s, level=lvl)

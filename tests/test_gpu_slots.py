@@ -217,3 +217,27 @@ def test_vcycle_leaves_running_slots(n, precision, iters):
         S.st.synchronize()
         for a, b in zip(got, want):
             assert torch.equal(a, b), how
+
+
+@pytest.mark.parametrize("n,precision", [(32, "mixed"), (64, "mixed"), (64, "fp64")])
+def test_filling_and_emptying_keeps_the_bits(n, precision):
+    """The operator's block order changes with the share of busy slots (7/8 of them,
+    from 64^3 up): slots that live through both orders give what they give alone."""
+    torch, P, _ = _setup()
+    say(f"engine filled and emptied n={n} {precision}")
+    slots = 17
+    S = Slots(n, precision, slots, busy=0)
+    xi = P.noise(n, 7, batch=slots)
+    want = S.box.sample(xi, u_box=True)["u_box"]
+    torch.cuda.synchronize()                 # the slots use the handle's buffers on another stream
+    S.start([])
+    for s in range(slots):                   # filled one by one, emptied as they finish
+        S.check(S.L.spde_slot_start_seeded(S.h, s, 7, s, 0, S.sp))
+        S.step(4 if s == 15 else 1)
+    left = set(range(slots))
+    while left:
+        for s in [t for t in S.run(3, want=1) if t in left]:
+            got = S.finish(s)
+            S.st.synchronize()
+            assert torch.equal(got, want[s]), s
+            left.remove(s)
