@@ -609,8 +609,11 @@ std::string tune_key(Ctx* c) {
   // batch class of the context's largest batch: 1, 2..15, 16+
   const char* cls = c->max_batch == 1 ? "b1" : (c->max_batch < 16 ? "b2" : "b16");
   char buf[128];
-  // t2: the finest up kernel is timed together with the operator pass that reads its output
-  snprintf(buf, sizeof buf, "%s:n%d:%s:%s:t2", arch.c_str(), c->n, c->fp64() ? "fp64" : "mixed", cls);
+  // t3: version of the kernels and of their timing that a choice belongs to (the finest
+  // up kernel timed together with the operator pass that reads its output; 3-D tiles
+  // in runs along z; short launches timed apart from their issue).  Choices of another
+  // version in a file are passed over.
+  snprintf(buf, sizeof buf, "%s:n%d:%s:%s:t3", arch.c_str(), c->n, c->fp64() ? "fp64" : "mixed", cls);
   return buf;
 }
 
