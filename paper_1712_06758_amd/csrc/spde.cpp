@@ -112,7 +112,8 @@ struct Ctx {
   int ring = kRing;             // entries of the zhat ring (kRing, or fewer in a smaller workspace)
   int unapplied = 0;            // updates that an iterating slot may have waiting after a step (at most ring)
   int slots_hi = 0;             // slots [0, slots_hi) have been initialised since the workspace was bound
-  std::vector<char> started;    // [max_batch] slots that were started and not yet fetched
+  std::vector<char> started;    // [max_batch] slots that were started and not yet fetched (2: found
+                                // finished by a poll since the last step)
   hipStream_t own_stream = nullptr;
   hipStream_t aux_stream = nullptr;   // second half of a split batch
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -411,12 +412,10 @@ spde_status enqueue_operator(Ctx* c, const View& V, int batch, hipStream_t st, i
   return SPDE_OK;
 }
 
-// Direction pass over the slots of V (`count` iterations up to `iter` are
-// waiting): every slot's, or the finished slots' only.
-spde_status enqueue_direction(Ctx* c, const View& V, int batch, hipStream_t st, int iter, int count,
-                              bool finished_only = false) {
+// Direction pass over the slots of V (`count` iterations up to `iter` are waiting).
+spde_status enqueue_direction(Ctx* c, const View& V, int batch, hipStream_t st, int iter, int count) {
   Timed t(c, KID_DIRECTION, iter, st, count, V.s0, batch);
-  HIPCHK(launch_direction(c->fp64(), V.F, c->box, batch, finished_only, st));
+  HIPCHK(launch_direction(c->fp64(), V.F, c->box, batch, st));
   return SPDE_OK;
 }
 
@@ -440,7 +439,7 @@ spde_status enqueue_iteration(Ctx* c, const View& V, int batch, hipStream_t st, 
 // kernels take their state from the per-slot scalars.
 spde_status get_graph(Ctx* c, const View& V, int batch, hipStream_t st, hipGraphExec_t* out, int L) {
   const int64_t key =
-      ((int64_t)V.F.spread << 60) | ((int64_t)V.s0 << 40) | ((int64_t)L << 24) | (int64_t)batch;
+      ((int64_t)V.F.finish << 61) | ((int64_t)V.F.spread << 60) | ((int64_t)V.s0 << 40) | ((int64_t)L << 24) | (int64_t)batch;
   auto it = c->graphs.find(key);
   if (it != c->graphs.end()) { *out = it->second; return SPDE_OK; }
   hipGraph_t g = nullptr;
@@ -1497,8 +1496,8 @@ spde_status spde_slot_start_seeded(spde_handle h, int slot, uint64_t seed, uint6
 // of 32^3 mixed 1.03, 1.07, 1.11, 1.27.
 static int spread_slots(const Ctx* c, int nslots) {
   if (c->n < 64) return 1;
-  const int64_t busy = std::count(c->started.begin(), c->started.begin() + nslots, 1);
-  return 8 * busy < 7 * (int64_t)nslots;
+  const int64_t idle = std::count(c->started.begin(), c->started.begin() + nslots, 0);
+  return 8 * idle > (int64_t)nslots;
 }
 
 spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) {
@@ -1511,6 +1510,10 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
   hipStream_t st = pick_stream(c, stream);
   const bool graphs = c->use_graphs && c->timing != 1 && st != nullptr;
   View V0 = make_view(c, 0);
+  // A slot that finishes gets its waiting updates in the iteration that finds it so:
+  // no later call then has anything to add to its field or can disturb it, on
+  // whatever stream it runs.  The others' updates wait until the ring is full.
+  V0.F.finish = 1;
   V0.F.spread = spread_slots(c, nslots);
   // A caller may be capturing the stream and replay these launches any number
   // of times: the direction passes are then part of what is captured, with
@@ -1521,10 +1524,10 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
     s = enqueue_direction(c, V0, c->slots_hi, st, 0, c->ring);
     if (s != SPDE_OK) return s;
   }
-  const int most = std::min({iters, c->poll, c->ring});   // iterations of a chunk
+  for (char& v : c->started) v = v ? 1 : 0;
   int waiting = captured ? 0 : c->unapplied;
   for (int done = 0; done < iters;) {
-    const int chunk = std::min(iters - done, most);
+    const int chunk = std::min({iters - done, c->poll, c->ring});
     if (waiting + chunk > c->ring) {
       s = enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
       if (s != SPDE_OK) return s;
@@ -1536,14 +1539,8 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
     if (!captured) c->unapplied = waiting;
     done += chunk;
   }
-  // A step leaves the fields of the slots that have finished final, so that no
-  // later call has anything to add to them or can disturb them, on whatever
-  // stream it runs; the others' updates may wait for as long as the ring holds
-  // another step's.
-  if (!captured && waiting + most <= c->ring) return enqueue_direction(c, V0, nslots, st, 0, waiting, true);
-  s = enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
-  if (s == SPDE_OK && !captured) c->unapplied = 0;
-  return s;
+  if (captured) return enqueue_direction(c, V0, c->slots_hi, st, 0, waiting);
+  return SPDE_OK;
 }
 
 spde_status spde_slots_poll(spde_handle h, int nslots, int* state_host, int* iters_host, void* stream) {
@@ -1564,6 +1561,7 @@ spde_status spde_slots_poll(spde_handle h, int nslots, int* state_host, int* ite
       case ST_FAILED: code = 3; break;
       default: code = 4;
     }
+    if (c->started[i]) c->started[i] = v.state == ST_DONE ? 2 : 1;
     if (state_host) state_host[i] = code;
     if (iters_host) iters_host[i] = v.iters;
   }
@@ -1577,7 +1575,8 @@ spde_status spde_slot_finish(spde_handle h, int slot, double* u_box_dev, void* s
   if (slot < 0 || slot >= c->max_batch) return fail(SPDE_EINVAL, "slot out of range");
   HIPCHK(hipSetDevice(c->device));
   hipStream_t st = pick_stream(c, stream);
-  if (c->unapplied || being_captured(st)) {   // a slot that still iterates; a finished one has nothing waiting
+  // a slot that still iterates; a finished one has nothing waiting
+  if ((c->unapplied && c->started[slot] != 2) || being_captured(st)) {
     s = enqueue_direction(c, make_view(c, slot), 1, st, 0, c->ring);
     if (s != SPDE_OK) return s;
   }

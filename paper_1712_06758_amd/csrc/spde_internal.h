@@ -211,6 +211,7 @@ struct Fields {
   double* part_up;   // [slot][nb_up][2] partial sums of <zhat, v_u>, zhat^T A zhat
   double* part_pb;   // [slot][nb_pb]    partial sums of q |v_sigma|^2
   Scalars* sc;       // [slot]
+  int finish;        // slots that are found finished get their waiting updates in the same iteration
   int spread;        // many slots are idle: deal the slots of an operator launch out to the XCDs in turn
 };
 
@@ -290,10 +291,9 @@ hipError_t launch_operator(bool z_fp64, const Fields& F, const Box& bx, int batc
 bool small_box(const Box& bx, const Level& top);
 hipError_t launch_small(bool fp64, const Fields& F, const Box& bx, const Level& top, const Level& next,
                         const void* cinv, int batch, int iters, hipStream_t st);
-// Apply the waiting direction and solution updates of the slots, or of the
-// finished ones only (a slot with none is left as it is).
-hipError_t launch_direction(bool z_fp64, const Fields& F, const Box& bx, int batch, bool finished_only,
-                            hipStream_t st);
+// Apply the waiting direction and solution updates of the slots (a slot with
+// none is left as it is).
+hipError_t launch_direction(bool z_fp64, const Fields& F, const Box& bx, int batch, hipStream_t st);
 hipError_t launch_fix_solution(const Fields& F, const Box& bx, int batch, int slot0, hipStream_t st);
 hipError_t launch_flux(const double* u, double* sig_int, double* sig_ext, const Box& bx, int batch,
                        hipStream_t st);

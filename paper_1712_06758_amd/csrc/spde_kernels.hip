@@ -117,14 +117,14 @@ template <> struct ZVec<double> { using type = dbl2; };
 template <> struct ZVec<float> { using type = flt4; };
 
 template <typename TZ, bool NT>
-__global__ __launch_bounds__(kBlock) void k_direction(Fields F, int64_t nc, int nb, bool finished_only) {
+__global__ __launch_bounds__(kBlock) void k_direction(Fields F, int64_t nc, int nb) {
   using VZ = typename ZVec<TZ>::type;
   constexpr int V = 16 / sizeof(TZ), H = V / 2;   // cells per thread, double pairs per thread
   int slot, blk;
   slot_block(blockIdx.x, gridDim.x, nb, slot, blk);
   Scalars* S = F.sc + slot;
   const int state = S->state;
-  if (state != ST_DONE && (state != ST_ACTIVE || finished_only)) return;
+  if (state != ST_ACTIVE && state != ST_DONE) return;
   const int jf = S->jf, m = min(S->pit - jf, F.zm + 1);
   if (m <= 0) return;
   const int64_t c = ((int64_t)blk * kBlock + threadIdx.x) * V;

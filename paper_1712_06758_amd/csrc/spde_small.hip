@@ -52,7 +52,8 @@ struct SmallLayout {
 // Threads own columns of C cells along z (cells (i, j, C q .. C q + C - 1)), so
 // that the z neighbours, the z window of the faces and the pairs of the
 // restriction are mostly a thread's own.
-template <typename TM, int LN, int POLY>
+// FIN: a sample that finishes gets the updates it has waiting before the launch ends.
+template <typename TM, int LN, int POLY, bool FIN>
 __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx, SmallLevels P, int iters) {
   using S = SmallLayout<TM, LN>;
   constexpr int n = S::n, N = S::N, T = S::T, PL = n * n, PP = S::PP, C = S::C, Q = n / C;
@@ -343,19 +344,28 @@ __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx,
       }
     }
   }
+  if constexpr (FIN) {
+    if (ss->state == ST_DONE && ss->pit > ss->jf) {
+      const int jf = ss->jf, m = ss->pit - jf;
+      for (int r = 0; r < C; ++r)   // (a thread reads the zhat that it wrote)
+        finish_cells<TM>(F, slot, nc, jf, m, ss->flags & FL_ACCUM, c0 + r * PL, c0 + r * PL + 1, 1);
+      __syncthreads();
+      if (tid == 0) ss->jf = ss->pit;
+    }
+  }
   if (tid == 0) *SC = *ss;
 }
 
 bool small_box(const Box& bx, const Level& top) { return (bx.n == 8 || bx.n == 16) && !bx.kap && !top.dg; }
 
-template <typename TM, int LN, int POLY>
+template <typename TM, int LN, int POLY, bool FIN>
 static hipError_t launch_small_one(const Fields& F, const Box& bx, const SmallLevels& P, int batch, int iters,
                                    hipStream_t st) {
   using S = SmallLayout<TM, LN>;
-  const hipError_t e = hipFuncSetAttribute((const void*)k_small<TM, LN, POLY>,
+  const hipError_t e = hipFuncSetAttribute((const void*)k_small<TM, LN, POLY, FIN>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_small<TM, LN, POLY>), dim3(batch), dim3(S::T), S::bytes, st, F, bx, P, iters);
+  hipLaunchKernelGGL((k_small<TM, LN, POLY, FIN>), dim3(batch), dim3(S::T), S::bytes, st, F, bx, P, iters);
   return hipGetLastError();
 }
 
@@ -367,9 +377,11 @@ hipError_t launch_small(bool fp64, const Fields& F, const Box& bx, const Level& 
   P.lv[0] = top;
   P.lv[1] = next;
   P.cinv = cinv;
-#define SPDE_SMALL(TM, LN)                                                          \
-  return bx.poly ? launch_small_one<TM, LN, 1>(F, bx, P, batch, iters, st) \
-                 : launch_small_one<TM, LN, 0>(F, bx, P, batch, iters, st)
+#define SPDE_SMALL(TM, LN)                                                                              \
+  return F.finish ? (bx.poly ? launch_small_one<TM, LN, 1, true>(F, bx, P, batch, iters, st)            \
+                             : launch_small_one<TM, LN, 0, true>(F, bx, P, batch, iters, st))           \
+                  : (bx.poly ? launch_small_one<TM, LN, 1, false>(F, bx, P, batch, iters, st)           \
+                             : launch_small_one<TM, LN, 0, false>(F, bx, P, batch, iters, st))
   if (bx.n == 16) {
     if (fp64) SPDE_SMALL(double, 4);
     SPDE_SMALL(float, 4);
