@@ -406,9 +406,12 @@ spde_status enqueue_vpart(Ctx* c, const View& V, int batch, hipStream_t st, int 
   return SPDE_OK;
 }
 
-spde_status enqueue_operator(Ctx* c, const View& V, int batch, hipStream_t st, int iter) {
+// (last: the last one of a chunk of iterations)
+spde_status enqueue_operator(Ctx* c, const View& V, int batch, hipStream_t st, int iter, bool last) {
   Timed t(c, KID_OPERATOR, iter, st, 0, V.s0, batch);
-  HIPCHK(launch_operator(c->fp64(), V.F, c->box, batch, st));
+  Fields F = V.F;
+  if (!last) F.finish = 0;
+  HIPCHK(launch_operator(c->fp64(), F, c->box, batch, st));
   return SPDE_OK;
 }
 
@@ -427,10 +430,10 @@ bool being_captured(hipStream_t st) {
   return cap == hipStreamCaptureStatusActive;
 }
 
-spde_status enqueue_iteration(Ctx* c, const View& V, int batch, hipStream_t st, int iter) {
+spde_status enqueue_iteration(Ctx* c, const View& V, int batch, hipStream_t st, int iter, bool last) {
   spde_status s = enqueue_vpart(c, V, batch, st, iter);
   if (s != SPDE_OK) return s;
-  return enqueue_operator(c, V, batch, st, iter);
+  return enqueue_operator(c, V, batch, st, iter, last);
 }
 
 // Graph of L half-iterations for the slots of V, captured on first use:
@@ -447,7 +450,7 @@ spde_status get_graph(Ctx* c, const View& V, int batch, hipStream_t st, hipGraph
   c->capturing = true;
   spde_status s = SPDE_OK;
   for (int h = 0; h < L && s == SPDE_OK; ++h)
-    s = (h & 1) ? enqueue_operator(c, V, batch, st, 0) : enqueue_vpart(c, V, batch, st, 0);
+    s = (h & 1) ? enqueue_operator(c, V, batch, st, 0, h == L - 1) : enqueue_vpart(c, V, batch, st, 0);
   c->capturing = false;
   hipError_t e = hipStreamEndCapture(st, &g);
   if (s != SPDE_OK) { if (g) hipGraphDestroy(g); return s; }
@@ -493,7 +496,7 @@ spde_status enqueue_chunk(Ctx* c, const View& V, int batch, hipStream_t st, bool
   if (graphs && c->timing == 2) {
     bool ok = launch_graph(c, V, batch, st, 1);   // V-part of iteration 0
     for (int k = 0; ok && k < count; k += kTimedStride) {
-      spde_status s = enqueue_operator(c, V, batch, st, iter0 + k + 1);
+      spde_status s = enqueue_operator(c, V, batch, st, iter0 + k + 1, k == count - 1);
       if (s != SPDE_OK) return s;
       const int next = k + kTimedStride;
       // iterations k+1 .. next-1 whole, then the V-part of `next` (or the rest of the block)
@@ -507,7 +510,7 @@ spde_status enqueue_chunk(Ctx* c, const View& V, int batch, hipStream_t st, bool
     if (launch_graph(c, V, batch, st, 2 * count)) return SPDE_OK;
   }
   for (int k = 0; k < count; ++k) {
-    spde_status s = enqueue_iteration(c, V, batch, st, iter0 + k + 1);
+    spde_status s = enqueue_iteration(c, V, batch, st, iter0 + k + 1, k == count - 1);
     if (s != SPDE_OK) return s;
   }
   return SPDE_OK;
@@ -1510,9 +1513,9 @@ spde_status spde_slots_step(spde_handle h, int nslots, int iters, void* stream) 
   hipStream_t st = pick_stream(c, stream);
   const bool graphs = c->use_graphs && c->timing != 1 && st != nullptr;
   View V0 = make_view(c, 0);
-  // A slot that finishes gets its waiting updates in the iteration that finds it so:
-  // no later call then has anything to add to its field or can disturb it, on
-  // whatever stream it runs.  The others' updates wait until the ring is full.
+  // A step leaves the slots that have finished with no updates waiting: no later
+  // call then has anything to add to their fields or can disturb them, on whatever
+  // stream it runs.  The others' updates wait until the ring is full.
   V0.F.finish = 1;
   V0.F.spread = spread_slots(c, nslots);
   // A caller may be capturing the stream and replay these launches any number

@@ -211,7 +211,7 @@ struct Fields {
   double* part_up;   // [slot][nb_up][2] partial sums of <zhat, v_u>, zhat^T A zhat
   double* part_pb;   // [slot][nb_pb]    partial sums of q |v_sigma|^2
   Scalars* sc;       // [slot]
-  int finish;        // slots that are found finished get their waiting updates in the same iteration
+  int finish;        // a launch leaves the slots that have finished with no updates waiting
   int spread;        // many slots are idle: deal the slots of an operator launch out to the XCDs in turn
 };
 

@@ -347,10 +347,10 @@ __global__ __launch_bounds__(LN == 4 ? 512 : 128) void k_small(Fields F, Box bx,
   if constexpr (FIN) {
     if (ss->state == ST_DONE && ss->pit > ss->jf) {
       const int jf = ss->jf, m = ss->pit - jf;
-      for (int r = 0; r < C; ++r)   // (a thread reads the zhat that it wrote)
-        finish_cells<TM>(F, slot, nc, jf, m, ss->flags & FL_ACCUM, c0 + r * PL, c0 + r * PL + 1, 1);
+      const int own = (int)(threadIdx.x & (PL - 1)) + PL * C * (int)(threadIdx.x >> (2 * LN));
+      finish_cells<TM>(F, blockIdx.x, nc, jf, m, ss->flags & FL_ACCUM, own, own + PL * C, PL);   // (the zhat it wrote)
       __syncthreads();
-      if (tid == 0) ss->jf = ss->pit;
+      if (threadIdx.x == 0) ss->jf = jf + m;
     }
   }
   if (tid == 0) *SC = *ss;

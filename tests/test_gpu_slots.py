@@ -193,8 +193,9 @@ def test_vcycle_leaves_running_slots(n, precision, iters):
     want = [S.finish(s) for s in range(2)]
     r = torch.randn(2, n ** 3, generator=torch.Generator(device="cuda").manual_seed(9), device="cuda",
                     dtype=torch.float64)
+    torch.cuda.synchronize()
     z0 = S.box.apply_vcycle(r)
-    S.st.synchronize()
+    torch.cuda.synchronize()
     z = torch.empty_like(r)
     g = torch.cuda.CUDAGraph()               # captured while nothing waits
     with torch.cuda.graph(g, stream=S.st):
@@ -228,8 +229,9 @@ def test_filling_and_emptying_keeps_the_bits(n, precision):
     slots = 17
     S = Slots(n, precision, slots, busy=0)
     xi = P.noise(n, 7, batch=slots)
-    want = S.box.sample(xi, u_box=True)["u_box"]
     torch.cuda.synchronize()                 # the slots use the handle's buffers on another stream
+    want = S.box.sample(xi, u_box=True)["u_box"]
+    torch.cuda.synchronize()
     S.start([])
     for s in range(slots):                   # filled one by one, emptied as they finish
         S.check(S.L.spde_slot_start_seeded(S.h, s, 7, s, 0, S.sp))
