@@ -243,3 +243,29 @@ def test_filling_and_emptying_keeps_the_bits(n, precision):
             S.st.synchronize()
             assert torch.equal(got, want[s]), s
             left.remove(s)
+
+
+@pytest.mark.parametrize("face", [0, 1])
+@pytest.mark.parametrize("n,precision", [(16, "mixed"), (32, "fp64"), (64, "mixed"), (64, "fp64")])
+def test_cellwise_slots(n, precision, face):
+    """Slots of a box with a kappa field, in every operator form: finished in the step
+    that finds them so, with the fields of a sampling call."""
+    torch, P, _ = _setup()
+    say(f"cell-wise slots n={n} {precision} face block {face}")
+    S = Slots(n, precision, 2, busy=0)
+    S.box.set_face_preconditioner(face)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    S.box.set_coefficients(kappa=10.0 * torch.exp(0.3 * torch.randn(n ** 3, generator=g, device="cuda",
+                                                                    dtype=torch.float64)))
+    xi = P.noise(n, 7, batch=2)
+    torch.cuda.synchronize()
+    want = S.box.sample(xi, u_box=True)["u_box"]
+    torch.cuda.synchronize()
+    for iters in (1, 4):
+        S.start(range(2))
+        S.run(iters, want=2)
+        _call(S.box, torch, "operator", 2)
+        for s in range(2):
+            got = S.finish(s)
+            S.st.synchronize()
+            assert torch.equal(got, want[s]), (iters, s)
