@@ -69,9 +69,9 @@ struct alignas(16) DirCoef {
 // then leaves W and x alone (32 of its 132 bytes per cell in mixed precision),
 // and one direction pass moves 48 + kRing sizeof(zhat) bytes per cell for kRing
 // iterations.  Operator pass with the updates, without them, and direction pass
-// per iteration: 3.37 -> 2.56 + 0.31 ms (mixed, 128^3 x 64), 188 -> 148 + 16 us
+// per iteration: 3.37 -> 2.60 + 0.18 ms (mixed, 128^3 x 64), 188 -> 149 + 16 us
 // (float64, 64^3 x 32).  At 128^3 x 1 in float64, where the old pass ran out of
-// the last-level cache: 45.5 -> 38.7 + 5.1 us; 8 entries would leave 7.8 us
+// the last-level cache: 45.5 -> 35.6 + 4.9 us; 8 entries would leave 7.8 us
 // there, since each pass brings W and x back from memory.  The ring costs kRing
 // sizeof(zhat) bytes of memory per cell.  A workspace with less has a shorter one,
 // of 8, 4 or 2 entries (two: the memory of a double buffer), and

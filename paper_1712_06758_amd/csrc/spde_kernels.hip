@@ -839,14 +839,14 @@ __global__ void k_probe_scalars(Scalars* sc, int batch) {
   sc[s] = v;
 }
 
-// Scalars of a steady-state iteration (with the previous vectors, zhat in the
-// ring's first entry) for timing the operator pass; the coefficients are zero,
-// so whatever the vectors hold, nothing is read at a data-dependent place.
 // Keeps a stream busy while the launches behind it are issued (autotuner).
 __global__ void k_hold() {
   for (int k = 0; k < 24; ++k) __builtin_amdgcn_s_sleep(127);   // 127 x 64 cycles each
 }
 
+// Scalars of a steady-state iteration (with the previous vectors, zhat in the
+// ring's first entry) for timing the operator pass; the coefficients are zero,
+// so whatever the vectors hold, nothing is read at a data-dependent place.
 __global__ void k_tune_scalars(Scalars* sc, int batch) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= batch) return;

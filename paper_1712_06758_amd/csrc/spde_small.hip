@@ -5,10 +5,10 @@
 // are what other threads read), the rest in registers, and one LDS array that
 // the smoothing stages share.  Launched kernel by kernel, an iteration of a 16^3
 // box is five launches of a few blocks each and takes 33 us (float64); here it is
-// a chain of 17 block barriers and takes 12 us (28,900 cycles: the nine stages of
+// a chain of 16 block barriers and takes 12 us (28,900 cycles: the nine stages of
 // the finest level 5,300, the 8^3 and 4^3 levels 7,000, the face windows and
 // sums 11,300, the operator and the scalar step 5,300): a call on one 16^3 sample
-// 1366 -> 680 us.  It is bound by the FP64 issue and the latencies of one compute
+// 1366 -> 648 us.  It is bound by the FP64 issue and the latencies of one compute
 // unit; batches run side by side on the others.
 //
 // The arithmetic is that of the level, coarse, scalar and operator kernels,
