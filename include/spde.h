@@ -532,7 +532,7 @@ spde_status spde_set_poll_interval(spde_handle h, int iters);
  *   enable = 0 stops and keeps the totals; -1 clears the totals (the mode
  *   is kept).
  * Boxes of 8^3 and 16^3 with constant kappa run whole iterations in one launch
- * (class iterations_small, recorded in mode 1). */
+ * (class iterations_small, recorded in modes 1 and 2). */
 spde_status spde_timing(spde_handle h, int enable);
 int         spde_kernel_count(void);
 const char* spde_kernel_name(int id);

@@ -279,7 +279,7 @@ struct Timed {
   Timed(Ctx* c_, int kid_, int iter_, hipStream_t st_, int level_ = 0, int s0_ = 0, int nslots_ = -1,
         double bytes_ = -1.0)
       : c(c_), kid(kid_), iter(iter_), level(level_), s0(s0_), nslots(nslots_), st(st_), bytes(bytes_) {
-    on = !c->capturing && (c->timing == 1 || (c->timing == 2 && kid == KID_OPERATOR));
+    on = !c->capturing && (c->timing == 1 || (c->timing == 2 && (kid == KID_OPERATOR || kid == KID_SMALL)));
     if (!on) return;
     e0 = next_event(c);
     if (e0) hipEventRecord(e0, st);
